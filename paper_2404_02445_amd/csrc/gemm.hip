@@ -836,761 +836,481 @@ __global__ __launch_bounds__(WM * WN * KS * 64) void gemm_kernel(const GemmParam
     }
 }
 
-// Wide products (bf16, dense A, large M, N and K; see gemm_wide_class): 256 x 256 block tiles on
-// v_mfma_f32_32x32x16_bf16.  Four waves each own a 128 x 128 quadrant -- 16 accumulator tiles of
-// 32 x 32, 256 registers per lane, which the compiler keeps in the accumulation half of the
-// register file -- so one block fills a CU, one wave per SIMD.  (A single wave per SIMD issues
-// the 32 x 32 x 16 MFMA at ~90 % of the peak rate but the 16 x 16 x 32 one at ~55 %, measured.)
-// A stage holds 64 k (64 KB: 256 rows of A and of B, one cache line each) and costs one
-// barrier; two stages in LDS.  Per stage a CU moves 64 KB for 8.4 MFLOP (128 FLOP/B, twice the
-// 128 x 128 tile's) and a wave reads 32 KB of fragments for 64 MFMAs.  Each 16-wide k step's
-// MFMAs run while the next step's fragments are read, so LDS reads always overlap MFMAs, and the
-// next stage's loads are spread over the first k step.  Operand loads (whole-line rows into
-// XOR-swizzled LDS blocks) are gemm_kernel's; the MFMA shape is not, so an operator whose
-// (M, N, K) puts it here runs here for every sub-slice launch, and every output element sees the
-// same operations in the same order whatever the sub-slice count.
-constexpr int kWideRowB = 256 * 2 + 16, kWideRowF = 256 * 4 + 16;   // staged output row strides, bytes
-constexpr int kWideBStages = 2;                                      // B stages in LDS
-constexpr int kWideGroupM = 8;                                       // m tiles per group in the block order
-// An accumulator read out where it is used (left to itself the compiler copies many accumulator
-// tiles to ordinary registers at once, and spills them)
-__device__ __forceinline__ float acc_read(float a) {
-    float v;
-    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(a));
-    return v;
-}
+// ---------------------------------------------------------------------------
+// Large bf16 products (see pp_class): 256 x 256 block tiles on v_mfma_f32_32x32x16_bf16, eight
+// waves in two groups that take turns on the matrix units.
+//
+// Waves 0-3 (one per SIMD) own the upper 128 rows of the tile, waves 4-7 the lower ones, each a
+// 128 x 64 part (8 accumulator tiles, 128 registers).  A 64-wide k tile is worked in two phases,
+// the upper and the lower half of the wave's rows (A0, A1) against all its columns, 16 MFMAs each.
+// A phase is a memory step (fragment reads from LDS, operand loads) and an MFMA step with a barrier
+// after each, and the second group runs one step behind the first: while one wave of a SIMD
+// multiplies, the other reads and loads, so neither the LDS reads nor the issue of the loads (which
+// hold a wave for ~50 cycles each) leave the matrix unit idle.  A step costs a few tens of
+// instructions and a barrier whatever it does, so the phases are as large as the registers allow
+// (four phases of 8 MFMAs, with longer load distances: 877 against 785 us on 8192 x 8192 x 8192).
+//
+// Each operand's stage is two 16 KB halves, two stages in LDS (128 KB).  A0 and both halves of B are
+// read in the first phase and reloaded for the k tile after next in the second; A1 is read in the
+// second and reloaded in the first of the next k tile: at the end of every memory step the loads
+// the next one needs are a k tile old (~2300 cycles) and the eight issued since stay in flight.
+//
+// A block runs up to kPPChunk tiles; the load stream goes on into the next tile during the last k
+// tiles of the current one, so set-up and first-stage latency are paid once per block.  The 32
+// blocks an XCD runs at a time work on 32 consecutive tiles of its run, in groups of 8 m tiles
+// that share operand rows in its L2.  The results are stored from the accumulators: a lane holds
+// four consecutive columns, and a half-wave swap makes them eight (one 16-byte store).
+//
+// Arithmetic: acc = sum over k in 16-wide steps in ascending order from zero, then + (bias +
+// bias2), + residual, activation: a function of the op alone, so tiles run across the edges of
+// sub-slices (a sub-slice narrower than a tile would leave the rest of it empty: 4096 x 768 -> 2304 in
+// 8 sub-slices of 288 columns took 27.1 us with two tiles each, 23.6 us so).
+//
+// What bounds it: with 16 of the 256 CUs busy a k tile takes 0.94 us (the MFMAs alone 0.87 us at
+// 2.36 GHz); with all of them 1.5 us, the clock the chip holds under that load (8192 x 8192 x 8192: 778-800
+// us, with a zero operand 629 us; independent MFMAs alone: 1950 TFLOP/s on random data, 2490 on zeros).  Measured
+// against the kernels it replaced (128 x 128 tiles of gemm_kernel, and four waves of 128 x 128 with
+// one stage of prefetch for the largest products): 8192 x 1024 -> 32000 580 -> 472 us, VGG-16's
+// 3x3 convs over 56 x 56 x 256 at batch 16 75 -> 56 us, 8192 x 256 -> 8002 188 -> 72 us.  Not kept: four phases
+// per k tile (above), waiting for the reads after the barrier instead of before it (931 against 877
+// us), all eight waves in step with the next k step read under each (847 against 803 us), stores
+// with the non-temporal policy (694 against 514 us), blocks started apart so that their stores
+// do not meet (531 against 520 us), 4 m tiles per group (531 against 514 us).
+// ---------------------------------------------------------------------------
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-template <int NB>
-__global__ __launch_bounds__(256, 1) void gemm_wide_kernel(const GemmParams p) {
-    using T = __bf16;
-    constexpr int BM = 256, BN = 256, TM = 128, TN = 128;
-    constexpr int FM = TM / 32, FN = TN / 32;   // 32 x 32 MFMA tiles per wave
-    constexpr int NBA = BM / 8, NBB = BN / 8;   // 1 KB blocks (8 rows x 128 bytes) per operand stage
-    constexpr int NW = 4;
-    constexpr int LA = NBA / NW, LB = NBB / NW; // load slots per wave (8 + 8)
-    constexpr int SA = NBA * 64, SB = NBB * 64; // uint4 per A stage and per B stage (32 KB each)
-    constexpr int BK = 64;
-    static_assert(NB == 2 || NB == 3, "B stages in LDS");
-    // LDS: two A stages, then NB B stages; the epilogue's staged tile (256 rows of bf16 or 128 rows
-    // of float32, rows padded by 16 bytes) reuses the space
-    constexpr int OPS_U4 = 2 * SA + NB * SB;
-    constexpr int TILE_U4 = (BM * kWideRowB > TM * kWideRowF ? BM * kWideRowB : TM * kWideRowF) / 16;
-    __shared__ uint4 lds[OPS_U4 > TILE_U4 ? OPS_U4 : TILE_U4];
+constexpr int kPPTile = 256;
+constexpr int kPPChunk = 4;        // most tiles of one block
+constexpr int kPPGroupM = 8;       // m tiles per group in the block order
 
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
-
-    touch_kernargs<sizeof(GemmParams)>();
-    const unsigned t = (blockIdx.x % 8) * static_cast<unsigned>(p.g_per_xcd) + blockIdx.x / 8;
-    if (t >= static_cast<unsigned>(p.g_total)) return;
-    constexpr int GM = kWideGroupM;
-    const unsigned group = p.g_div_group.div(t);
-    const unsigned within = t - group * static_cast<unsigned>(GM * p.g_cols);
-    const bool last = static_cast<int>(group) == (p.g_mt - 1) / GM;
-    const unsigned gm = last ? static_cast<unsigned>(p.g_mt - group * GM) : GM;
-    const unsigned colu = last ? p.g_div_last.div(within) : within / GM;
-    const int mti = static_cast<int>(group * GM + (within - colu * gm));
-    const unsigned c1 = p.g_div_nt.div(colu);
-    const int nti = static_cast<int>(colu - c1 * static_cast<unsigned>(p.g_nt));
-    const int j = static_cast<int>(c1);         // one split: the column index is the sub-slice
-
-    const int q = p.g_q, rr = p.g_rr;
-    const int n_lo = j * q + min(j, rr), n_hi = (j + 1) * q + min(j + 1, rr);
-    const int n0 = n_lo + nti * BN;
-    if (n0 >= n_hi) return;
-    const int Mi = static_cast<int>(p.M);
-    const int m0 = mti * BM;
-    const int nk = p.g_nk;                      // >= 1 (K >= 64 here)
-
-    // operand loads: gemm_kernel's layout (8 whole rows per 1 KB block, chunk (l % 8) ^ row)
-    const int cl = (lane & 7) ^ (lane >> 3);
-    unsigned voffA[LA], voffB[LB];
-#pragma unroll
-    for (int i = 0; i < LA; ++i) {
-        const int m = m0 + (wave + NW * i) * 8 + (lane >> 3);
-        const int mc = m < Mi ? m : Mi - 1;
-        voffA[i] = static_cast<unsigned>(mc) * static_cast<unsigned>(p.lda * sizeof(T)) + static_cast<unsigned>(cl * 16);
-    }
-#pragma unroll
-    for (int i = 0; i < LB; ++i) {
-        const int n = n0 + (wave + NW * i) * 8 + (lane >> 3);
-        const int nc = n < n_hi ? n : n_hi - 1;
-        voffB[i] = static_cast<unsigned>(nc) * static_cast<unsigned>(p.K * sizeof(T)) + static_cast<unsigned>(cl * 16);
-    }
-    const int ktail = (p.K % BK) ? nk - 1 : nk;
-    uint4* const ldsA = &lds[0];
-    uint4* const ldsB = &lds[2 * SA];
-    // Load slots 2 i, 2 i + 1 of operand X's stage kt into LDS stage buffer buf.  A stage past
-    // the last one re-reads the last one (into a buffer nobody reads), so that every iteration
-    // issues the same loads and the wait counts stay exact.
-    auto issue_a = [&](int kt, int buf, int i) __attribute__((always_inline)) {
-        kt = kt < nk ? kt : nk - 1;
-        const unsigned soff = static_cast<unsigned>(kt) * (BK * sizeof(T));
-        const bool kin = kt != ktail || kt * BK + cl * 8 < p.K;
-#pragma unroll
-        for (int s2 = 2 * i; s2 < 2 * i + 2; ++s2)
-            buffer_load_lds(p.A, p.a_bytes, (lds_ptr_t)(ldsA + buf * SA + (wave + NW * s2) * 64), kin ? voffA[s2] : kOOB, soff);
-    };
-    auto issue_b = [&](int kt, int buf, int i) __attribute__((always_inline)) {
-        kt = kt < nk ? kt : nk - 1;
-        const unsigned soff = static_cast<unsigned>(kt) * (BK * sizeof(T));
-        const bool kin = kt != ktail || kt * BK + cl * 8 < p.K;
-#pragma unroll
-        for (int s2 = 2 * i; s2 < 2 * i + 2; ++s2)
-            buffer_load_lds(p.B, p.b_bytes, (lds_ptr_t)(ldsB + buf * SB + (wave + NW * s2) * 64), kin ? voffB[s2] : kOOB, soff);
-    };
-    static_assert(LA == LB && LA == 2 * FM, "two load slots per row of fragments");
-
-    // MFMA layout (weight fragment first): accumulator register r of tile (a, b) holds output
-    // row m = m0 + wm TM + 32 a + l % 32 and column n = n0 + wn TN + 32 b + 8 (r / 4) + 4 (l / 32)
-    // + r % 4: four groups of four consecutive columns per lane
-    const int lrow = lane & 31, lhalf = lane >> 5;
-    // bias + second bias, as gemm_kernel starts a direct launch (partial groups read up front)
-    const T* biasp = static_cast<const T*>(p.bias);
-    const T* bias2p = static_cast<const T*>(p.bias2);
-    Raw4<T> rb[FN][4], rb2[FN][4];
-    float bslow[FN][4][4];
-#pragma unroll
-    for (int b = 0; b < FN; ++b)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int n = n0 + wn * TN + b * 32 + g * 8 + lhalf * 4;
-            const int nv = max(0, min(4, n_hi - n));
-            const bool fast = nv == 4;
-            rb[b][g] = load_raw4<T>(fast && biasp ? biasp + n : nullptr, kZeroChunk);
-            rb2[b][g] = load_raw4<T>(fast && bias2p ? bias2p + n : nullptr, kZeroChunk);
-            float bv[4], b2v[4];
-            ld4_or_zero<T>(biasp, n, fast ? 0 : nv, bv);
-            ld4_or_zero<T>(bias2p, n, fast ? 0 : nv, b2v);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) bslow[b][g][e] = bv[e] + b2v[e];
-        }
-
-    // prologue: B stage 0, A stage 0 and, with three B buffers, B stage 1
-    static_for<FM>([&](auto i) __attribute__((always_inline)) { issue_b(0, 0, i); });
-    static_for<FM>([&](auto i) __attribute__((always_inline)) { issue_a(0, 0, i); });
-    if constexpr (NB == 3) static_for<FM>([&](auto i) __attribute__((always_inline)) { issue_b(1, 1, i); });
-
-    f32x16 acc[FM][FN];
-#pragma unroll
-    for (int b = 0; b < FN; ++b)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int n = n0 + wn * TN + b * 32 + g * 8 + lhalf * 4;
-            const bool fast = n + 4 <= n_hi;
-            float bv[4], b2v[4];
-            unpack4<T>(rb[b][g], bv);
-            unpack4<T>(rb2[b][g], b2v);
-#pragma unroll
-            for (int a = 0; a < FM; ++a)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[a][b][4 * g + e] = fast ? bv[e] + b2v[e] : bslow[b][g][e];
-        }
-
-    // LDS byte offset of this lane's fragment (row l % 32 of a 32-row group, k chunk 2 kk + l / 32
-    // of the stage) for k step kk, within stage buffer 0 of A (fa) and of B (fb), for the wave's
-    // first rows; fragment a (b) of the wave sits 32 a (32 b) rows = 4 KB further
-    const unsigned ldsa0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_ptr_t)ldsA));
-    const unsigned ldsb0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_ptr_t)ldsB));
-    unsigned fa[4], fb[4];
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        const unsigned f = ((lrow >> 3) * 64 + (lrow & 7) * 8 + ((2 * kk + lhalf) ^ (lrow & 7))) * 16;
-        fa[kk] = ldsa0 + f + ((wm * TM) >> 3) * 1024;
-        fb[kk] = ldsb0 + f + ((wn * TN) >> 3) * 1024;
-    }
-    // One k step: the MFMAs on fragments (ma, mb), row of tiles by row, each row preceded by
-    // the reads of another k step's fragments a and b (into ra, rb, from LDS at ra_base,
-    // rb_base) and, when kt >= 0, by load slots: rows 0 and 1 load A stage kt + 1 into A buffer
-    // (kt + 1) % 2, rows 2 and 3 load B stage kt + NB - 1 into B buffer (kt + NB - 1) % NB (the
-    // B loads go out last, so that a wait for all but them covers the A loads).  Nothing is
-    // scheduled across the rows.
-    auto step = [&](u32x4 (&ma)[FM], u32x4 (&mb)[FN], unsigned ra_base, unsigned rb_base, u32x4 (&ra)[FM],
-                    u32x4 (&rb)[FN], int kt, int bbuf_next) __attribute__((always_inline)) {
-        static_for<FM>([&](auto a) __attribute__((always_inline)) {
-            ra[a] = lds_read16_at<a * 4096>(ra_base);
-            rb[a] = lds_read16_at<a * 4096>(rb_base);
-            if (kt >= 0) {
-                if constexpr (a < 2)
-                    issue_a(kt + 1, (kt + 1) & 1, 2 * a), issue_a(kt + 1, (kt + 1) & 1, 2 * a + 1);
-                else
-                    issue_b(kt + NB - 1, bbuf_next, 2 * (a - 2)), issue_b(kt + NB - 1, bbuf_next, 2 * (a - 2) + 1);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int b = 0; b < FN; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, mb[b]),
-                                                                    __builtin_bit_cast(bf16x8, ma[a]), acc[a][b], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        });
-    };
-    auto read_all = [&](unsigned ra_base, unsigned rb_base, u32x4 (&ra)[FM], u32x4 (&rb)[FN]) __attribute__((always_inline)) {
-        static_for<FM>([&](auto a) __attribute__((always_inline)) {
-            ra[a] = lds_read16_at<a * 4096>(ra_base);
-            rb[a] = lds_read16_at<a * 4096>(rb_base);
-        });
-    };
-    auto pin_all = [&](u32x4 (&af)[FM], u32x4 (&bf)[FN]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int a = 0; a < FM; ++a) pin(af[a]);
-#pragma unroll
-        for (int b = 0; b < FN; ++b) pin(bf[b]);
-    };
-    // wait until this wave's loads of A stage st and B stage st have landed: with three B
-    // buffers the eight B loads issued last (B stage st + 1) may still be in flight
-    auto wait_stage = [&]() __attribute__((always_inline)) {
-        if constexpr (NB == 3)
-            asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-        else
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    };
-
-    // Stage st sits in A buffer st % 2 and B buffer st % NB.  Iteration st: wait for it, barrier
-    // (every wave's share has landed; stage st - 1 is fully read), then four k steps; step kk
-    // multiplies the fragments of the step before it (step 3 of stage st - 1 for kk = 0) while it
-    // reads its own, and step 0 also loads A stage st + 1 and B stage st + NB - 1.
-    u32x4 f0a[FM], f0b[FN], f1a[FM], f1b[FN];
-    wait_stage();
-    __builtin_amdgcn_s_barrier();
-    read_all(fa[0], fb[0], f0a, f0b);
-    lds_wait();
-    pin_all(f0a, f0b);
-    step(f0a, f0b, fa[1], fb[1], f1a, f1b, 0, (NB - 1) % NB);
-    lds_wait();
-    pin_all(f1a, f1b);
-    step(f1a, f1b, fa[2], fb[2], f0a, f0b, -1, 0);
-    lds_wait();
-    pin_all(f0a, f0b);
-    step(f0a, f0b, fa[3], fb[3], f1a, f1b, -1, 0);
-    lds_wait();
-    pin_all(f1a, f1b);
-    int bcur = 0;                                      // B buffer of stage st
-    for (int st = 1; st < nk; ++st) {
-        bcur = bcur == NB - 1 ? 0 : bcur + 1;
-        const int bnext = bcur == 0 ? NB - 1 : bcur - 1;   // (st + NB - 1) % NB: stage st - 1's buffer
-        const unsigned abase = (st & 1) * SA * 16, bbase = bcur * SB * 16;
-        wait_stage();                                  // this wave's share of stage st has landed
-        __builtin_amdgcn_s_barrier();                  // every wave's has; stage st - 1 fully read
-        step(f1a, f1b, abase + fa[0], bbase + fb[0], f0a, f0b, st, bnext);
-        lds_wait();
-        pin_all(f0a, f0b);
-        step(f0a, f0b, abase + fa[1], bbase + fb[1], f1a, f1b, -1, 0);
-        lds_wait();
-        pin_all(f1a, f1b);
-        step(f1a, f1b, abase + fa[2], bbase + fb[2], f0a, f0b, -1, 0);
-        lds_wait();
-        pin_all(f0a, f0b);
-        step(f0a, f0b, abase + fa[3], bbase + fb[3], f1a, f1b, -1, 0);
-        lds_wait();
-        pin_all(f1a, f1b);
-    }
-#pragma unroll
-    for (int a = 0; a < FM; ++a)
-#pragma unroll
-        for (int b = 0; b < FN; ++b)
-            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f1b[b]),
-                                                                __builtin_bit_cast(bf16x8, f1a[a]), acc[a][b], 0, 0, 0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last (unread) loads land before LDS is reused
-
-    // --- epilogue ---------------------------------------------------------------------------
-    // Without a residual and with a bf16 output, v = act(acc) is rounded in the MFMA layout and
-    // the bf16 tile is staged in LDS in one pass; otherwise the float32 sums are staged in two
-    // passes of 128 rows and finished in 8-column chunks as gemm_kernel finishes them (residual,
-    // activation, rounding).  Either way the stores are whole 16-byte chunks along rows, and a
-    // pass reads all its residual chunks before its first store, so that no wait in the epilogue
-    // waits for a store.
-    __syncthreads();                                   // every wave is done with the operand stages
-    unsigned char* tile = reinterpret_cast<unsigned char*>(lds);
-    const int tid = threadIdx.x;
-    const T* resp = static_cast<const T*>(p.res);
-    if (!resp && !p.out_f32) {
-        // (one copy of the unrolled tile per activation: a per-element choice would evaluate
-        // every activation for all 256 values)
-        auto stage_bf16 = [&](auto act) __attribute__((always_inline)) {
-            static_for<FM>([&](auto a) __attribute__((always_inline)) {
-                static_for<FN>([&](auto b) __attribute__((always_inline)) {
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        float v[4];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] = act_f(acc_read(acc[a][b][4 * g + e]) + 0.0f, decltype(act)::value);
-                        const int row = wm * TM + a * 32 + lrow, col = wn * TN + b * 32 + g * 8 + lhalf * 4;
-                        *reinterpret_cast<bf16x4*>(tile + row * kWideRowB + col * 2) =
-                            bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
-                    }
-                    // one tile at a time: the accumulators are read out only when they are used
-                    __builtin_amdgcn_sched_barrier(0);
-                });
-            });
-        };
-        if (p.act == MOPAR_ACT_RELU)
-            stage_bf16(std::integral_constant<int, MOPAR_ACT_RELU>{});
-        else if (p.act == MOPAR_ACT_GELU)
-            stage_bf16(std::integral_constant<int, MOPAR_ACT_GELU>{});
-        else
-            stage_bf16(std::integral_constant<int, MOPAR_ACT_NONE>{});
-        __syncthreads();
-        T* C = static_cast<T*>(p.C);
-        for (int i = 0; i < BM / 8; ++i) {
-            const int r = i * 8 + (tid >> 5), c = (tid & 31) * 8;
-            const int m = m0 + r, n = n0 + c;
-            if (m >= Mi || n >= n_hi) continue;
-            const uint4 w = *reinterpret_cast<const uint4*>(tile + r * kWideRowB + c * 2);
-            T* dst = C + static_cast<int64_t>(m) * p.ldc + n;
-            const int nv = min(8, n_hi - n);
-            if (nv == 8 && aligned16(dst)) {
-                *reinterpret_cast<uint4*>(dst) = w;
-            } else {
-                const unsigned short* h = reinterpret_cast<const unsigned short*>(&w);
-                for (int e = 0; e < nv; ++e) reinterpret_cast<unsigned short*>(dst)[e] = h[e];
-            }
-        }
-        return;
-    }
-    constexpr int NCH = TM * BN / 8 / 256;             // 8-column chunks per thread and pass
-    const int cc = tid & 31, cr = tid >> 5;            // chunk column; first row (then every 8th)
-    const int c0 = n0 + cc * 8;
-    const int cval = max(0, min(8, n_hi - c0));
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        if (h) __syncthreads();                        // the first half's rows are all read
-        if (wm == h) {
-            static_for<FM>([&](auto a) __attribute__((always_inline)) {
-                static_for<FN>([&](auto b) __attribute__((always_inline)) {
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int row = a * 32 + lrow, col = wn * TN + b * 32 + g * 8 + lhalf * 4;
-                        *reinterpret_cast<f32x4*>(tile + row * kWideRowF + col * 4) =
-                            f32x4{acc_read(acc[a][b][4 * g]), acc_read(acc[a][b][4 * g + 1]),
-                                  acc_read(acc[a][b][4 * g + 2]), acc_read(acc[a][b][4 * g + 3])};
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                });
-            });
-        }
-        __syncthreads();
-        Raw8<T> rraw[NCH];
-        bool rfast[NCH];
-        if (resp) {
-#pragma unroll
-            for (int i = 0; i < NCH; ++i) {
-                const int m = m0 + h * TM + cr + 8 * i;
-                const int64_t idx = static_cast<int64_t>(m) * p.ldc + c0;
-                rfast[i] = m < Mi && cval == 8 && aligned16(resp + idx);
-                rraw[i] = load_raw8<T>(rfast[i] ? resp + idx : nullptr, kZeroChunk);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < NCH; ++i) {
-            const int r = cr + 8 * i;
-            const int m = m0 + h * TM + r;
-            if (m >= Mi || cval == 0) continue;
-            float v[8], rsd[8];
-            const f32x4 lo = *reinterpret_cast<const f32x4*>(tile + r * kWideRowF + cc * 32);
-            const f32x4 hi = *reinterpret_cast<const f32x4*>(tile + r * kWideRowF + cc * 32 + 16);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = lo[e], v[4 + e] = hi[e];
-            const int64_t idx = static_cast<int64_t>(m) * p.ldc + c0;
-            if (resp && rfast[i])
-                unpack8<T>(rraw[i], rsd);
-            else
-                load8<T>(resp, idx, resp ? cval : 0, rsd);
-            if (p.act == MOPAR_ACT_NONE) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = v[e] + rsd[e];
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = act_f(v[e] + rsd[e], p.act);
-            }
-            if (p.out_f32)
-                store8<float>(static_cast<float*>(p.C), idx, v, cval);
-            else
-                store8<T>(static_cast<T*>(p.C), idx, v, cval);
-        }
-    }
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), static_cast<short>(0), bytes, kRsrcWord3);
 }
+// the low (0) or high (1) bf16 of a word
+__device__ __forceinline__ float bf16_of(unsigned w, int hi) { return __uint_as_float(hi ? w & 0xffff0000u : w << 16); }
 
-// Persistent form of gemm_wide_kernel, used when the launch brings tile counters (one word per
-// XCD, zeroed by the launcher before the launch): one block per CU, fed from a queue.  The blocks
-// of XCD x take x's run of tiles, first one each by block index, then from x's counter, so that a
-// block whose CU is busy with another stream's kernel when the launch starts takes fewer tiles,
-// and the blocks an XCD runs together still work on neighbouring tiles.  Per tile the MFMA
-// arithmetic is gemm_wide_kernel's.  What changes is the hand-over between tiles: the next
-// tile's number is fetched while the current tile's first stage runs, its first stage is loaded
-// during the current tile's last stage, its bias while the current tile is stored, and the
-// epilogue stores straight from the accumulators (one store per group of four columns, an
-// out-of-range offset for the groups that are not written, so that every tile issues the same
-// number of stores and the next tile waits for its first stage without waiting for them).  It
-// takes products without a residual or an activation (the others run on gemm_wide_kernel).
-__global__ __launch_bounds__(256, 1) void gemm_wide_persistent(const GemmParams p) {
+// epilogues: bf16 results in whole aligned groups of eight columns, without and with a residual,
+// float32 results (no residual or activation), and bf16 results of any width and alignment
+enum { PP_BF16 = 0, PP_RES = 1, PP_F32 = 2, PP_ANY = 3 };
+// eight bf16 at any address (the hardware takes unaligned 16-byte accesses)
+__device__ __forceinline__ u32x4 load_any16(const void* q) {
+    u32x4 v;
+    __builtin_memcpy(&v, __builtin_assume_aligned(q, 2), 16);
+    return v;
+}
+__device__ __forceinline__ void store_any16(void* q, u32x4 v) { __builtin_memcpy(__builtin_assume_aligned(q, 2), &v, 16); }
+
+template <bool CONV, int EPI, int ACT>
+__global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
     using T = __bf16;
-    constexpr int BM = 256, BN = 256, TM = 128, TN = 128;
-    constexpr int FM = TM / 32, FN = TN / 32;
-    constexpr int NBA = BM / 8, NBB = BN / 8;
-    constexpr int NW = 4;
-    constexpr int LA = NBA / NW, LB = NBB / NW;
-    constexpr int SA = NBA * 64, SB = NBB * 64;
-    constexpr int BK = 64;
-    constexpr int NSTORE = FM * FN * 4;          // stores per lane and tile (regular tiles)
-    static_assert(LA == LB && LA == 2 * FM, "two load slots per row of fragments");
-    static_assert(NSTORE == 64, "the first-stage wait below lets 63 stores stay in flight");
-    __shared__ uint4 lds[2 * SA + 2 * SB];
-    __shared__ int s_ticket;
-    __shared__ __attribute__((aligned(16))) float s_bias[BN];
-
+    constexpr unsigned HALF = 16384, STAGE = 4 * HALF;   // bytes: A0 A1 B0 B1
+    __shared__ uint4 lds[2 * STAGE / 16];
+    touch_kernargs<sizeof(GemmParams)>();
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = wave >> 2, wn = wave & 3;
     const int lrow = lane & 31, lhalf = lane >> 5;
-    touch_kernargs<sizeof(GemmParams)>();
 
-    const int xcd = blockIdx.x & 7, gx = static_cast<int>(gridDim.x >> 3);
-    const int t_lo = xcd * p.g_per_xcd;
-    const int cx = min(p.g_per_xcd, p.g_total - t_lo);   // tiles of this XCD's run
-    unsigned* const ctr = p.wide_ctr + xcd;
-    const int Mi = static_cast<int>(p.M);
-    const int nk = p.g_nk;                               // >= 2 (checked at launch)
-    const int ktail = (p.K % BK) ? nk - 1 : nk;
-    const int cl = (lane & 7) ^ (lane >> 3);
-
-    // tile li of this XCD's run -> rows m0.., columns n0 .. n_hi - 1; false when the tile lies
-    // past a narrower sub-slice's last column
-    auto decode = [&](int li, int& m0, int& n0, int& n_hi) __attribute__((always_inline)) -> bool {
-        const unsigned t = static_cast<unsigned>(t_lo + li);
-        constexpr int GM = kWideGroupM;
+    // --- the block's tiles: j-th is number first + 32 j of its XCD's run -------------------------
+    const int t_lo = static_cast<int>(blockIdx.x & 7) * p.g_per_xcd;
+    const int t_end = min(p.g_per_xcd, p.g_total - t_lo);
+    const int li = static_cast<int>(blockIdx.x >> 3);
+    int t_next = (li >> 5) * 32 * p.g_chunk + (li & 31);
+    const int t_last = min(t_end, ((li >> 5) + 1) * 32 * p.g_chunk);
+    struct Tile { int m0, n0; };
+    auto take = [&](Tile& tl) __attribute__((always_inline)) -> bool {   // the next tile of the block
+        if (t_next >= t_last) return false;
+        const unsigned t = static_cast<unsigned>(t_lo + t_next);
+        t_next += 32;
         const unsigned group = p.g_div_group.div(t);
-        const unsigned within = t - group * static_cast<unsigned>(GM * p.g_cols);
-        const bool last = static_cast<int>(group) == (p.g_mt - 1) / GM;
-        const unsigned gm = last ? static_cast<unsigned>(p.g_mt - group * GM) : GM;
-        const unsigned colu = last ? p.g_div_last.div(within) : within / GM;
-        const int mti = static_cast<int>(group * GM + (within - colu * gm));
-        const unsigned c1 = p.g_div_nt.div(colu);
-        const int nti = static_cast<int>(colu - c1 * static_cast<unsigned>(p.g_nt));
-        const int j = static_cast<int>(c1);
-        const int n_lo = j * p.g_q + min(j, p.g_rr);
-        n_hi = (j + 1) * p.g_q + min(j + 1, p.g_rr);
-        n0 = n_lo + nti * BN;
-        m0 = mti * BM;
-        return n0 < n_hi;
+        const unsigned within = t - group * static_cast<unsigned>(kPPGroupM * p.g_nt);
+        const bool last = static_cast<int>(group) == (p.g_mt - 1) / kPPGroupM;
+        const unsigned gm = last ? static_cast<unsigned>(p.g_mt - group * kPPGroupM) : kPPGroupM;
+        const unsigned nti = last ? p.g_div_last.div(within) : within / kPPGroupM;
+        tl.n0 = __builtin_amdgcn_readfirstlane(static_cast<int>(nti) * kPPTile);
+        tl.m0 = __builtin_amdgcn_readfirstlane(static_cast<int>(group * kPPGroupM + (within - nti * gm)) * kPPTile);
+        return true;
     };
-    // one more tile number from the queue, the same for every thread of the block
-    auto fetch_now = [&]() __attribute__((always_inline)) -> int {
-        if (threadIdx.x == 0) s_ticket = gx + static_cast<int>(__hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        __syncthreads();
-        const int v = __builtin_amdgcn_readfirstlane(s_ticket);
-        __syncthreads();
-        return v;
-    };
-    auto offsets = [&](int m0, int n0, int n_hi, unsigned (&va)[LA], unsigned (&vb)[LB]) __attribute__((always_inline)) {
+    Tile cur, ahead;
+    if (!take(cur)) return;                    // block-uniform, before any barrier
+    ahead = cur;
+    bool live = true;                          // the load stream still has a tile
+
+    // --- operand loads ------------------------------------------------------------------------
+    // A half is 16 blocks of 1 KB (8 rows x 128 bytes); wave w loads blocks w and w + 8.  Chunk c of
+    // row r sits at place c ^ (r % 8) ^ (bit 4 of r): the 32-row fragment reads are then free of bank
+    // conflicts (a read serves lanes 0-3, 12-15, 20-23, 24-27 together, then 4-11, 16-19, 28-31;
+    // without bit 4 two of each group's rows meet in a bank: 292 against 510 B/ns per CU).  Row r of A half i is tile row 128 (r / 64) + 64 i + r % 64, row r
+    // of B half j tile column 64 (r / 32) + 32 j + r % 32: each wave's part of C is contiguous.
+    const int Mi = static_cast<int>(p.M);
+    const int nk = p.g_nk;                     // >= 2 (checked at launch)
+    const int ktail = (p.K % 64) ? nk - 1 : nk;
+    const int cl = (lane & 7) ^ (lane >> 3) ^ ((wave >> 1) & 1);
+    // Offsets of this lane's loads [half][slot]; a lane or tile with nothing to load holds kOOB.
+    // Dense: va, vb + 128 bytes per k tile (the scalar offset).  Conv: a k tile lies in one tap; vw is
+    // the offset of the window's corner (counted from a_lead bytes before A, so never negative), vmask
+    // has a bit per tap inside the image, va = vw or kOOB for the current tap, and the scalar offset is
+    // that of the tap's pixel and channel.
+    u32x4 va = {}, vb = {}, vw = {}, vmask = {};   // element 2 half + slot
+    const unsigned a_lead = CONV ? static_cast<unsigned>((p.pad * p.img_w + p.pad) * p.cs * 2) : 0u;
+    const unsigned char* const a_base = static_cast<const unsigned char*>(p.A) - a_lead;
+    const unsigned a_size = p.a_bytes + a_lead;
+    int ikt = 0, tap = 0, tcol = 0, tch = 0;   // k tile of the load stream; conv: its tap, tap column, first channel
+    unsigned koff_a = 0, koff_b = 0;           // its scalar offsets
+    unsigned lds_dst = static_cast<unsigned>(wave) * 64u;   // where this wave's loads go, in uint4 (stage 0 or 1)
+    auto offsets = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < LA; ++i) {
-            const int m = m0 + (wave + NW * i) * 8 + (lane >> 3);
-            const int mc = m < Mi ? m : Mi - 1;
-            va[i] = static_cast<unsigned>(mc) * static_cast<unsigned>(p.lda * sizeof(T)) + static_cast<unsigned>(cl * 16);
-        }
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int i = 0; i < LB; ++i) {
-            const int n = n0 + (wave + NW * i) * 8 + (lane >> 3);
-            const int nc = n < n_hi ? n : n_hi - 1;
-            vb[i] = static_cast<unsigned>(nc) * static_cast<unsigned>(p.K * sizeof(T)) + static_cast<unsigned>(cl * 16);
-        }
-    };
-    uint4* const ldsA = &lds[0];
-    uint4* const ldsB = &lds[2 * SA];
-    // Load slot s2 of one operand's stage kt (clamped to the last stage) into buffer buf.  (Issuing
-    // one of these 1 KB loads holds the wave for ~50 cycles, measured; the K loop puts one after
-    // every second MFMA, so that the MFMAs already issued keep the matrix unit busy meanwhile.)
-    auto load_a = [&](const unsigned (&va)[LA], int kt, int buf, int s2) __attribute__((always_inline)) {
-        kt = __builtin_amdgcn_readfirstlane(kt < nk ? kt : nk - 1);
-        const unsigned soff = static_cast<unsigned>(kt) * (BK * sizeof(T));
-        const bool kin = kt != ktail || kt * BK + cl * 8 < p.K;
-        // (the offset is settled before the load: a branch around the load would turn the
-        // scalar offset into a per-lane one, which the compiler then loops over)
-        unsigned v = kin ? va[s2] : kOOB;
-        asm volatile("" : "+v"(v));
-        buffer_load_lds(p.A, p.a_bytes, (lds_ptr_t)(ldsA + buf * SA + (wave + NW * s2) * 64), v, soff);
-    };
-    auto load_b = [&](const unsigned (&vb)[LB], int kt, int buf, int s2) __attribute__((always_inline)) {
-        kt = __builtin_amdgcn_readfirstlane(kt < nk ? kt : nk - 1);
-        const unsigned soff = static_cast<unsigned>(kt) * (BK * sizeof(T));
-        const bool kin = kt != ktail || kt * BK + cl * 8 < p.K;
-        // (the offset is settled before the load: a branch around the load would turn the
-        // scalar offset into a per-lane one, which the compiler then loops over)
-        unsigned v = kin ? vb[s2] : kOOB;
-        asm volatile("" : "+v"(v));
-        buffer_load_lds(p.B, p.b_bytes, (lds_ptr_t)(ldsB + buf * SB + (wave + NW * s2) * 64), v, soff);
-    };
-    // Bias + second bias of a tile: thread t reads column n0 + t (zero past n_hi) and the sums go
-    // through LDS (s_bias), from which every wave starts its accumulators -- the same float
-    // additions as gemm_kernel's, per column.
-    const T* biasp = static_cast<const T*>(p.bias);
-    const T* bias2p = static_cast<const T*>(p.bias2);
-    auto bias_col = [&](int n0, int n_hi, float& bv, float& b2v) __attribute__((always_inline)) {
-        const int n = n0 + static_cast<int>(threadIdx.x);
-        bv = (biasp && n < n_hi) ? ld_f(biasp, n) : 0.0f;
-        b2v = (bias2p && n < n_hi) ? ld_f(bias2p, n) : 0.0f;
-    };
-    f32x16 acc[FM][FN];
-    auto bias_init = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int b = 0; b < FN; ++b)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const f32x4 bsum = *reinterpret_cast<const f32x4*>(&s_bias[wn * TN + b * 32 + g * 8 + lhalf * 4]);
-#pragma unroll
-                for (int a = 0; a < FM; ++a)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[a][b][4 * g + e] = bsum[e];
+            for (int s = 0; s < 2; ++s) {
+                const int r = (wave + 8 * s) * 8 + (lane >> 3);
+                const int m = min(ahead.m0 + (r >> 6) * 128 + h * 64 + (r & 63), Mi - 1);
+                const int n = min(ahead.n0 + (r >> 5) * 64 + h * 32 + (r & 31), p.N - 1);
+                if constexpr (CONV) {
+                    const unsigned mu = static_cast<unsigned>(m);
+                    const unsigned img = p.div_hw.div(mu);
+                    const unsigned rem = mu - img * static_cast<unsigned>(p.out_h * p.out_w);
+                    const unsigned ho = p.div_w.div(rem), wo = rem - ho * static_cast<unsigned>(p.out_w);
+                    const int hb = static_cast<int>(ho) * p.stride - p.pad, wb = static_cast<int>(wo) * p.stride - p.pad;
+                    vw[2 * h + s] = static_cast<unsigned>((static_cast<int>(img) * p.img_h + hb) * p.img_w + wb) *
+                                   static_cast<unsigned>(p.cs * 2) + static_cast<unsigned>(cl * 16) + a_lead;
+                    unsigned mask = 0;
+                    for (int tr = 0, bit = 0; tr < p.kh; ++tr)
+                        for (int tc = 0; tc < p.kw; ++tc, ++bit)
+                            if (static_cast<unsigned>(hb + tr) < static_cast<unsigned>(p.img_h) &&
+                                static_cast<unsigned>(wb + tc) < static_cast<unsigned>(p.img_w))
+                                mask |= 1u << bit;
+                    vmask[2 * h + s] = mask;
+                    va[2 * h + s] = (mask & 1u) ? vw[2 * h + s] : kOOB;
+                } else {
+                    va[2 * h + s] = static_cast<unsigned>(m) * static_cast<unsigned>(p.lda * 2) + static_cast<unsigned>(cl * 16);
+                }
+                vb[2 * h + s] = static_cast<unsigned>(n) * static_cast<unsigned>(p.K * 2) + static_cast<unsigned>(cl * 16);
             }
     };
+    auto load_a = [&](auto h) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+            buffer_load_lds(a_base, a_size, (lds_ptr_t)(lds + lds_dst + h * (HALF / 16) + s * 512), va[2 * h + s], koff_a);
+    };
+    auto load_b = [&](auto h) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+            buffer_load_lds(p.B, p.b_bytes, (lds_ptr_t)(lds + lds_dst + (2 + h) * (HALF / 16) + s * 512), vb[2 * h + s], koff_b);
+    };
+    // the load stream to the next k tile: of the same tile, or the first of the block's next one
+    auto stream_next = [&]() __attribute__((always_inline)) {
+        lds_dst ^= STAGE / 16;
+        koff_b += 128;
+        koff_a += 128;
+        ++ikt;
+        if (ikt == nk) {
+            ikt = tap = tcol = tch = 0;
+            koff_a = koff_b = 0;
+            live = live && take(ahead);
+            if (live) {
+                offsets();
+            } else {
+                va = vb = u32x4{kOOB, kOOB, kOOB, kOOB};
+                vmask = u32x4{};
+            }
+        } else if constexpr (CONV) {
+            tch += 64;
+            if (tch == p.cs) {                 // the next tap
+                tch = 0;
+                ++tap;
+                if (++tcol == p.kw) {
+                    tcol = 0;
+                    koff_a += static_cast<unsigned>((p.img_w - p.kw) * p.cs * 2);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) va[e] = ((vmask[e] >> tap) & 1u) ? vw[e] : kOOB;
+            }
+        } else {
+            if (ikt == ktail) {                // chunks past K
+                const bool past = ikt * 64 + cl * 8 >= p.K;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) va[e] = past ? kOOB : va[e], vb[e] = past ? kOOB : vb[e];
+            }
+        }
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
 
-    const unsigned ldsa0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_ptr_t)ldsA));
-    const unsigned ldsb0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_ptr_t)ldsB));
+    offsets();
+    load_b(I0{});                              // prologue: k tile 0, and k tile 1 but for A1 (nk >= 2)
+    load_b(I1{});
+    load_a(I0{});
+    load_a(I1{});
+    stream_next();
+    load_b(I0{});
+    load_b(I1{});
+    load_a(I0{});
+
+    // --- fragments ------------------------------------------------------------------------------
+    // lane's 16 bytes of k step kk (16 wide): row l % 32 of a 32-row tile, chunk 2 kk + l / 32
+    const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_ptr_t)(&lds[0])));
     unsigned fa[4], fb[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-        const unsigned f = ((lrow >> 3) * 64 + (lrow & 7) * 8 + ((2 * kk + lhalf) ^ (lrow & 7))) * 16;
-        fa[kk] = ldsa0 + f + ((wm * TM) >> 3) * 1024;
-        fb[kk] = ldsb0 + f + ((wn * TN) >> 3) * 1024;
+        const unsigned f = lds0 + (lrow >> 3) * 1024 + (lrow & 7) * 128 + (((2 * kk + lhalf) ^ (lrow & 7) ^ (lrow >> 4)) << 4);
+        fa[kk] = f + wm * 8192;
+        fb[kk] = f + wn * 4096;
     }
-    // One k step: MFMAs on (ma, mb) row by row, each row preceded by the reads of the next k step's
-    // fragments; loads(2 a + h) after the row's MFMA 2 h + 1.  Nothing is scheduled across.
-    auto step = [&](u32x4 (&ma)[FM], u32x4 (&mb)[FN], unsigned ra_base, unsigned rb_base, u32x4 (&ra)[FM],
-                    u32x4 (&rb_)[FN], auto&& loads) __attribute__((always_inline)) {
-        static_for<FM>([&](auto a) __attribute__((always_inline)) {
-            ra[a] = lds_read16_at<a * 4096>(ra_base);
-            rb_[a] = lds_read16_at<a * 4096>(rb_base);
-            __builtin_amdgcn_sched_barrier(0);
-            static_for<FN>([&](auto b) __attribute__((always_inline)) {
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, mb[b]),
-                                                                    __builtin_bit_cast(bf16x8, ma[a]), acc[a][b], 0, 0, 0);
-                if constexpr (b % 2 == 1) loads(2 * a + b / 2);
-                __builtin_amdgcn_sched_barrier(0);
-            });
+    u32x4 af[2][4], bf[2][4];
+    f32x16 acc[2][2][2];                       // [A half][row tile][B half]
+    bool stored = false;                       // the block has stored a tile, 16 stores or more a wave
+    // An MFMA step, after the reads and loads of its memory step: wait for the reads and for the loads
+    // that the next memory step reads, the eight issued since staying in flight (in a tile's first
+    // k tile the previous tile's 16 stores, or more, lie between them)
+    auto mfma_step = [&](auto i, auto first) __attribute__((always_inline)) {
+        if (decltype(first)::value && stored)
+            asm volatile("s_waitcnt vmcnt(24) lgkmcnt(0)" ::: "memory");
+        else
+            asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            pin(af[0][kk]), pin(af[1][kk]);
+            if constexpr (i == 0) pin(bf[0][kk]), pin(bf[1][kk]);
+        }
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][a][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bf[j][kk]),
+                                                                           __builtin_bit_cast(bf16x8, af[a][kk]), acc[i][a][j], 0, 0, 0);
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+    };
+    auto read_a = [&](auto h) __attribute__((always_inline)) {
+        static_for<4>([&](auto kk) __attribute__((always_inline)) {
+            af[0][kk] = lds_read16_at<h * HALF>(fa[kk]);
+            af[1][kk] = lds_read16_at<h * HALF + 4096>(fa[kk]);
         });
     };
-    auto no_loads = [](int) __attribute__((always_inline)) {};
-    auto pin_all = [&](u32x4 (&af)[FM], u32x4 (&bf)[FN]) __attribute__((always_inline)) {
+    auto read_b = [&]() __attribute__((always_inline)) {
+        static_for<4>([&](auto kk) __attribute__((always_inline)) {
+            bf[0][kk] = lds_read16_at<2 * HALF>(fb[kk]);
+            bf[1][kk] = lds_read16_at<3 * HALF>(fb[kk]);
+        });
+    };
+    auto ktile = [&](auto first) __attribute__((always_inline)) {
+        read_b();
+        read_a(I0{});
+        load_a(I1{});
+        stream_next();
+        mfma_step(I0{}, first);
+        read_a(I1{});
+        load_b(I0{});
+        load_b(I1{});
+        load_a(I0{});
 #pragma unroll
-        for (int a = 0; a < FM; ++a) pin(af[a]);
-#pragma unroll
-        for (int b = 0; b < FN; ++b) pin(bf[b]);
+        for (int kk = 0; kk < 4; ++kk) fa[kk] ^= STAGE, fb[kk] ^= STAGE;
+        mfma_step(I1{}, first);
     };
 
-    // --- first tile -------------------------------------------------------------------------
-    int li = static_cast<int>(blockIdx.x >> 3);
-    int m0 = 0, n0 = 0, n_hi = 0;
-    for (;;) {                                          // (block-uniform)
-        if (li >= cx) return;
-        if (decode(li, m0, n0, n_hi)) break;
-        li = fetch_now();
-    }
-    unsigned va[LA], vb[LB];
-    offsets(m0, n0, n_hi, va, vb);
-    int par = 0;                                        // stage s of the tile sits in buffers (par + s) & 1
-    {
-        float bv, b2v;
-        bias_col(n0, n_hi, bv, b2v);
-        s_bias[threadIdx.x] = bv + b2v;
-    }
-#pragma unroll
-    for (int s2 = 0; s2 < LB; ++s2) load_b(vb, 0, 0, s2);
-#pragma unroll
-    for (int s2 = 0; s2 < LA; ++s2) load_a(va, 0, 0, s2);
-    bool wait_all = true;                               // the first stage's loads are the newest in flight
-
-    const uint32_t esz = p.out_f32 ? 4u : 2u;
-    const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(p.C, static_cast<short>(0),
-                                                                         static_cast<int>(p.c_bytes), kRsrcWord3);
-    const bool c_aligned = (reinterpret_cast<uintptr_t>(p.C) & (4 * esz - 1)) == 0 && (p.ldc & 3) == 0;
-
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");    // B and A0 of k tile 0
+    __builtin_amdgcn_s_barrier();
+    if (wave >= 4) __builtin_amdgcn_s_barrier();        // the second group runs one step behind
     for (;;) {
-        u32x4 f0a[FM], f0b[FN], f1a[FM], f1b[FN];
-        int li_next = cx;                               // the next tile (>= cx: none)
-        int m0n = 0, n0n = 0, n_hin = 0;
-        bool next_ok = false;
-        unsigned van[LA], vbn[LB];
-        int ticket_v = 0;
-        float nbv = 0.0f, nb2v = 0.0f;                  // the next tile's bias column
-        auto take_ticket = [&]() __attribute__((always_inline)) {
-            // (the ticket's load was issued in stage 0; this wait is the stage wait's)
-            if (threadIdx.x == 0) s_ticket = ticket_v;
-        };
-        auto read_ticket = [&]() __attribute__((always_inline)) {
-            li_next = __builtin_amdgcn_readfirstlane(s_ticket);
-            // (uniform values, kept in scalar registers: otherwise the compiler may treat the
-            // branches on them as divergent and loop over the loads' scalar offsets)
-            next_ok = __builtin_amdgcn_readfirstlane((li_next < cx && decode(li_next, m0n, n0n, n_hin)) ? 1 : 0) != 0;
-            m0n = __builtin_amdgcn_readfirstlane(m0n);
-            n0n = __builtin_amdgcn_readfirstlane(n0n);
-            n_hin = __builtin_amdgcn_readfirstlane(n_hin);
-            if (next_ok) offsets(m0n, n0n, n_hin, van, vbn);
-        };
-
-        // stage 0
-        if (wait_all)
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        else
-            asm volatile("s_waitcnt vmcnt(63)" ::: "memory");
-        __builtin_amdgcn_s_barrier();                  // (also: s_bias holds this tile's bias)
-        bias_init();
-        {
-            const unsigned ab = (par & 1) * SA * 16, bb = (par & 1) * SB * 16;
-            const int nb = (par + 1) & 1;
-            if (threadIdx.x == 0)
-                ticket_v = gx + static_cast<int>(__hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-            static_for<FM>([&](auto a) __attribute__((always_inline)) {
-                f0a[a] = lds_read16_at<a * 4096>(ab + fa[0]);
-                f0b[a] = lds_read16_at<a * 4096>(bb + fb[0]);
-            });
-            lds_wait();
-            pin_all(f0a, f0b);
-            auto ld1b = [&](int s2) __attribute__((always_inline)) { load_b(vb, 1, nb, s2); };
-            auto ld1a = [&](int s2) __attribute__((always_inline)) { load_a(va, 1, nb, s2); };
-            step(f0a, f0b, ab + fa[1], bb + fb[1], f1a, f1b, ld1b);
-            lds_wait();
-            pin_all(f1a, f1b);
-            step(f1a, f1b, ab + fa[2], bb + fb[2], f0a, f0b, ld1a);
-            lds_wait();
-            pin_all(f0a, f0b);
-            step(f0a, f0b, ab + fa[3], bb + fb[3], f1a, f1b, no_loads);
-            lds_wait();
-            pin_all(f1a, f1b);
-        }
-        // stages 1 .. nk - 2: this tile's next stage
-        for (int st = 1; st < nk - 1; ++st) {
-            const int buf = (par + st) & 1;
-            const unsigned ab = buf * SA * 16, bb = buf * SB * 16;
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            if (st == 1) take_ticket();
-            __builtin_amdgcn_s_barrier();
-            if (st == 1) read_ticket();
-            auto ldnb = [&](int s2) __attribute__((always_inline)) { load_b(vb, st + 1, buf ^ 1, s2); };
-            auto ldna = [&](int s2) __attribute__((always_inline)) { load_a(va, st + 1, buf ^ 1, s2); };
-            step(f1a, f1b, ab + fa[0], bb + fb[0], f0a, f0b, ldnb);
-            lds_wait();
-            pin_all(f0a, f0b);
-            step(f0a, f0b, ab + fa[1], bb + fb[1], f1a, f1b, ldna);
-            lds_wait();
-            pin_all(f1a, f1b);
-            step(f1a, f1b, ab + fa[2], bb + fb[2], f0a, f0b, no_loads);
-            lds_wait();
-            pin_all(f0a, f0b);
-            step(f0a, f0b, ab + fa[3], bb + fb[3], f1a, f1b, no_loads);
-            lds_wait();
-            pin_all(f1a, f1b);
-        }
-        // last stage: the next tile's first stage (or, without one, this stage again, unread)
-        {
-            const int buf = (par + nk - 1) & 1;
-            const unsigned ab = buf * SA * 16, bb = buf * SB * 16;
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            if (nk == 2) take_ticket();
-            __builtin_amdgcn_s_barrier();
-            if (nk == 2) read_ticket();
-            if (next_ok) bias_col(n0n, n_hin, nbv, nb2v);  // used in the epilogue
-            auto ldxb = [&](int s2) __attribute__((always_inline)) {
-                if (next_ok) load_b(vbn, 0, buf ^ 1, s2); else load_b(vb, nk - 1, buf ^ 1, s2);
-            };
-            auto ldxa = [&](int s2) __attribute__((always_inline)) {
-                if (next_ok) load_a(van, 0, buf ^ 1, s2); else load_a(va, nk - 1, buf ^ 1, s2);
-            };
-            step(f1a, f1b, ab + fa[0], bb + fb[0], f0a, f0b, ldxb);
-            lds_wait();
-            pin_all(f0a, f0b);
-            step(f0a, f0b, ab + fa[1], bb + fb[1], f1a, f1b, ldxa);
-            lds_wait();
-            pin_all(f1a, f1b);
-            step(f1a, f1b, ab + fa[2], bb + fb[2], f0a, f0b, no_loads);
-            lds_wait();
-            pin_all(f0a, f0b);
-            step(f0a, f0b, ab + fa[3], bb + fb[3], f1a, f1b, no_loads);
-            lds_wait();
-            pin_all(f1a, f1b);
-        }
 #pragma unroll
-        for (int a = 0; a < FM; ++a)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int b = 0; b < FN; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f1b[b]),
-                                                                    __builtin_bit_cast(bf16x8, f1a[a]), acc[a][b], 0, 0, 0);
-
-        // --- epilogue of this tile ---------------------------------------------------------
-        // (every wave has read the bias of this tile long ago: s_bias takes the next one's)
-        if (next_ok) s_bias[threadIdx.x] = nbv + nb2v;
-        // a tile is regular when every group of four columns is whole or absent and aligned:
-        // then one 8-byte (bf16) or 16-byte (float32) store per group, else one per element
-        const bool regular = c_aligned && (n0 & 3) == 0 && (n_hi & 3) == 0;
-        static_for<FM>([&](auto a) __attribute__((always_inline)) {
-            static_for<FN>([&](auto b) __attribute__((always_inline)) {
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[i][a][j][e] = 0.0f;
+        ktile(std::true_type{});
+        for (int kt = 1; kt < nk; ++kt) ktile(std::false_type{});
+        // --- epilogue: rows m0 + 128 wm + 64 i + 32 a + l % 32, columns n0 + 64 wn + 32 j + 8 g + 4 (l / 32) ..
+        const int nb = cur.n0 + wn * 64;
+        if constexpr (EPI != PP_ANY) {
+            // results and residual go through buffer resources: a row or group that is not stored gets an
+            // offset past the end, so every lane issues the same stores
+            const auto crs = buffer_rsrc(p.C, static_cast<int>(p.c_bytes));
+            const auto rrs = buffer_rsrc(p.res, p.res ? static_cast<int>(p.c_bytes) : 0);
+            // the wave's 64 columns of bias, through the scalar cache: a vector load would be waited for
+            // behind the operand loads in flight (groups past the end re-read the last one)
+            u32x2 rb[2][4], rb2[2][4];
+            auto group_bias = [&](const void* base, int n) __attribute__((always_inline)) -> u32x2 {
+                const auto* src = (const __attribute__((address_space(4))) unsigned char*)(base ? base : kZeroChunk);
+                const u32x4 q = *(const __attribute__((address_space(4))) u32x4*)(src + (base ? min(n, p.N - 8) * 2 : 0));
+                return u32x2{lhalf ? q[2] : q[0], lhalf ? q[3] : q[1]};
+            };
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const int m = m0 + wm * TM + a * 32 + lrow;
-                    const int n = n0 + wn * TN + b * 32 + g * 8 + lhalf * 4;
-                    const int nv = m < Mi ? max(0, min(4, n_hi - n)) : 0;
-                    const unsigned off = (static_cast<unsigned>(m) * static_cast<unsigned>(p.ldc) + static_cast<unsigned>(n)) * esz;
-                    float v[4];
+                    rb[j][g] = group_bias(p.bias, nb + j * 32 + g * 8);
+                    if constexpr (EPI == PP_F32) rb2[j][g] = group_bias(p.bias2, nb + j * 32 + g * 8);
+                }
+            // byte offsets: row + column, either past the result when it is not stored (results span less
+            // than 2^31 bytes: 0x7fffffff plus any row, and 2^31 plus any column, lie past it)
+            constexpr unsigned ESZ = EPI == PP_F32 ? 4u : 2u;
+            auto row_off = [&](int ia) __attribute__((always_inline)) -> unsigned {
+                const int m = cur.m0 + wm * 128 + ia * 32 + lrow;
+                return m < Mi ? static_cast<unsigned>(m) * static_cast<unsigned>(p.ldc * ESZ) : kOOB;
+            };
+            // bf16: the group of eight columns a lane moves, 2 gp (lanes 0-31) or 2 gp + 1 (32-63); float32: the
+            // lane's four columns of group g
+            unsigned col_off[2][EPI == PP_F32 ? 4 : 2];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = acc_read(acc[a][b][4 * g + e]) + 0.0f;
-                    if (regular) {
-                        const unsigned o = nv == 4 ? off : kOOB;
-                        if (p.out_f32) {
-                            __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]),
-                                                                         __float_as_uint(v[2]), __float_as_uint(v[3])},
-                                                                   crs, static_cast<int>(o), 0, 0);
-                        } else {
-                            const bf16x4 h = {(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
-                            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, h), crs, static_cast<int>(o), 0, 0);
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int g = 0; g < (EPI == PP_F32 ? 4 : 2); ++g) {
+                    const int n = nb + j * 32 + (EPI == PP_F32 ? g * 8 + lhalf * 4 : (2 * g + lhalf) * 8);
+                    col_off[j][g] = n < p.N ? static_cast<unsigned>(n) * ESZ : 0x7fffffffu;
+                }
+            u32x4 rr[2][2];
+            auto load_res = [&](unsigned row) __attribute__((always_inline)) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int gp = 0; gp < 2; ++gp)
+                        rr[j][gp] = __builtin_amdgcn_raw_buffer_load_b128(rrs, static_cast<int>(row + col_off[j][gp]), 0, 0);
+            };
+            auto store_bf16 = [&]() __attribute__((always_inline)) {
+                static_for<4>([&](auto ia) __attribute__((always_inline)) {
+                    const unsigned row = row_off(ia);
+                    if constexpr (EPI == PP_RES) load_res(row);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+#pragma unroll
+                        for (int gp = 0; gp < 2; ++gp) {
+                            float rs[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+                            if constexpr (EPI == PP_RES) {
+                                const u32x4 q = rr[j][gp];
+                                const u32x2 s0 = __builtin_amdgcn_permlane32_swap(q[0], q[2], false, false);
+                                const u32x2 s1 = __builtin_amdgcn_permlane32_swap(q[1], q[3], false, false);
+#pragma unroll
+                                for (int h = 0; h < 2; ++h)
+                                    rs[h][0] = bf16_of(s0[h], 0), rs[h][1] = bf16_of(s0[h], 1), rs[h][2] = bf16_of(s1[h], 0),
+                                    rs[h][3] = bf16_of(s1[h], 1);
+                            }
+                            u32x2 pk[2];
+#pragma unroll
+                            for (int h = 0; h < 2; ++h) {
+                                const int g = 2 * gp + h;
+                                float v[4];
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) {
+                                    v[e] = acc[ia / 2][ia % 2][j][4 * g + e] + bf16_of(rb[j][g][e / 2], e & 1);
+                                    if constexpr (EPI == PP_RES) v[e] += rs[h][e];
+                                    v[e] = act_f(v[e], ACT);
+                                }
+                                pk[h] = __builtin_bit_cast(u32x2, bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]});
+                            }
+                            const u32x2 s0 = __builtin_amdgcn_permlane32_swap(pk[0][0], pk[1][0], false, false);
+                            const u32x2 s1 = __builtin_amdgcn_permlane32_swap(pk[0][1], pk[1][1], false, false);
+                            __builtin_amdgcn_raw_buffer_store_b128(u32x4{s0[0], s1[0], s0[1], s1[1]}, crs,
+                                                                   static_cast<int>(row + col_off[j][gp]), 0, 0);
                         }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            };
+            if constexpr (EPI == PP_F32) {
+                static_for<4>([&](auto ia) __attribute__((always_inline)) {
+                    const unsigned row = row_off(ia);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            u32x4 v;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) v[e] = __float_as_uint(acc[ia / 2][ia % 2][j][4 * g + e] +
+                                                       (bf16_of(rb[j][g][e / 2], e & 1) + bf16_of(rb2[j][g][e / 2], e & 1)));
+                            __builtin_amdgcn_raw_buffer_store_b128(v, crs, static_cast<int>(row + col_off[j][g]), 0, 0);
+                        }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            } else {
+                store_bf16();
+            }
+        } else {
+            // Whole groups of eight columns move as unaligned 16-byte accesses, the last, partial one
+            // element by element (only the last column tile has it).
+            const T* const biasp = static_cast<const T*>(p.bias);
+            const T* const resp = static_cast<const T*>(p.res);
+            T* const C = static_cast<T*>(p.C);
+            const bool tail = cur.n0 + kPPTile > p.N;
+            u32x2 rb[2][4];
+            const auto brs = buffer_rsrc(biasp, biasp ? p.N * 2 : 0);
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int o = (nb + j * 32 + g * 8 + lhalf * 4) * 2;
+                    if (tail) {
+                        unsigned h[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) h[e] = static_cast<unsigned short>(__builtin_amdgcn_raw_buffer_load_b16(brs, o + 2 * e, 0, 0));
+                        rb[j][g] = u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
                     } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const unsigned o = e < nv ? off + e * esz : kOOB;
-                            if (p.out_f32)
-                                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[e]), crs, static_cast<int>(o), 0, 0);
-                            else
-                                __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, (__bf16)v[e]),
-                                                                      crs, static_cast<int>(o), 0, 0);
-                        }
+                        rb[j][g] = u32x2{0u, 0u};
+                        if (biasp) rb[j][g] = *(const __attribute__((address_space(1))) u32x2*)(reinterpret_cast<const char*>(biasp) + o);
                     }
                 }
+            static_for<4>([&](auto ia) __attribute__((always_inline)) {
+                const int m = cur.m0 + wm * 128 + ia * 32 + lrow;
+                const int64_t row = static_cast<int64_t>(min(m, Mi - 1)) * p.ldc;
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int gp = 0; gp < 2; ++gp) {
+                        const int n = nb + j * 32 + (2 * gp + lhalf) * 8;
+                        const int nv = m < Mi ? p.N - n : 0;           // 8 or more: a whole group
+                        u32x4 q = {};
+                        if (resp) {
+                            if (nv >= 8) {
+                                q = load_any16(resp + row + n);
+                            } else if (nv > 0) {
+                                unsigned h[8];
+#pragma unroll
+                                for (int e = 0; e < 8; ++e) h[e] = e < nv ? __builtin_bit_cast(unsigned short, resp[row + n + e]) : 0u;
+                                q = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
+                            }
+                        }
+                        const u32x2 r0 = __builtin_amdgcn_permlane32_swap(q[0], q[2], false, false);
+                        const u32x2 r1 = __builtin_amdgcn_permlane32_swap(q[1], q[3], false, false);
+                        u32x2 pk[2];
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            const int g = 2 * gp + h;
+                            float v[4];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                v[e] = act_f((acc[ia / 2][ia % 2][j][4 * g + e] + bf16_of(rb[j][g][e / 2], e & 1)) +
+                                                 bf16_of(e < 2 ? r0[h] : r1[h], e & 1), ACT);
+                            pk[h] = __builtin_bit_cast(u32x2, bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]});
+                        }
+                        const u32x2 s0 = __builtin_amdgcn_permlane32_swap(pk[0][0], pk[1][0], false, false);
+                        const u32x2 s1 = __builtin_amdgcn_permlane32_swap(pk[0][1], pk[1][1], false, false);
+                        const u32x4 w = {s0[0], s1[0], s0[1], s1[1]};
+                        if (nv >= 8) {
+                            store_any16(C + row + n, w);
+                        } else if (nv > 0) {
+#pragma unroll
+                            for (int e = 0; e < 7; ++e)
+                                if (e < nv) reinterpret_cast<unsigned short*>(C + row + n)[e] = static_cast<unsigned short>(w[e / 2] >> (16 * (e & 1)));
+                        }
+                    }
                 __builtin_amdgcn_sched_barrier(0);
             });
-        });
-
-        // --- the next tile -------------------------------------------------------------------
-        if (next_ok) {
-            m0 = m0n, n0 = n0n, n_hi = n_hin;
-#pragma unroll
-            for (int i = 0; i < LA; ++i) va[i] = van[i], vb[i] = vbn[i];
-            par = (par + nk) & 1;
-            // its first stage went out before this tile's 64 stores (irregular tiles issue more)
-            wait_all = !regular;
-            continue;
         }
-        // no prefetched tile: take numbers until one is not empty (or the run is done)
-        li = li_next;
-        for (;;) {
-            if (li >= cx) return;
-            if (decode(li, m0, n0, n_hi)) break;
-            li = fetch_now();
-        }
-        offsets(m0, n0, n_hi, va, vb);
-        par = 0;
-        __syncthreads();                                // every wave is done with both buffers
-        {
-            float bv, b2v;
-            bias_col(n0, n_hi, bv, b2v);
-            s_bias[threadIdx.x] = bv + b2v;
-        }
-#pragma unroll
-        for (int s2 = 0; s2 < LB; ++s2) load_b(vb, 0, 0, s2);
-#pragma unroll
-        for (int s2 = 0; s2 < LA; ++s2) load_a(va, 0, 0, s2);
-        wait_all = true;
+        stored = EPI != PP_ANY;   // (there the number of stores issued depends on the lanes: counted as none)
+        // the load stream has at least begun the next tile (it runs two k tiles ahead)
+        if (!live) break;
+        cur = ahead;
     }
+    if (wave < 4) __builtin_amdgcn_s_barrier();         // the second group's last step
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // no load into LDS outlives the block
 }
 
 // Split-K finish: sum the partials in split order, then the usual epilogue.
@@ -1920,55 +1640,90 @@ static hipError_t launch_cfg(const GemmParams& params, int width, hipStream_t st
     return hipGetLastError();
 }
 
-// 256 x 256 tiles (bf16, dense A, one split, standard epilogue)
-static hipError_t launch_wide(const GemmParams& params, int width, hipStream_t st) {
+// Whether an operator runs on gemm_pp_kernel: a function of its (M, N, K), geometry and alignment-free
+// properties alone, never of the sub-slice count, so that all its sub-slice launches run the same
+// arithmetic (a tile may hold columns of several sub-slices).  A block fills a CU, so the line lies at
+// the share of the CUs that the last round of tiles leaves idle.  Measured against gemm_kernel's tiles
+// (us, this kernel / gemm_kernel): 4096 x 768 -> 2304, 144 tiles, 23.6 / 30.9; -> 3072, 192 tiles, 25.0 /
+// 30.3; 3x3 convs over 56 x 56 x 256, 147 tiles, 56 / 68.5; 98 tiles, 52.5 / 43.9; 8192 x 1024 -> 1024, 128
+// tiles, 26.6 / 24.1; and in two rounds 600 x 1024 -> 25047, 294 tiles, 63.4 / 55.9; 8192 x 768 -> 3072, 384
+// tiles, 45.6 / 54.5; 8229 x 312 -> 8000, 1056 tiles, 73 / 94.
+static bool pp_class(const GemmParams& p) {
+    // (the output span is addressed with 32-bit offsets, below the out-of-range offset 2^31)
+    const int64_t c_span = ((p.M - 1) * p.ldc + p.N) * (p.out_f32 ? 4 : 2);
+    if (p.thin || p.epi != EPI_STD || p.splits != 1 || c_span >= (int64_t(1) << 31)) return false;
+    // float32 results and second biases: the LSTM's input projection only
+    if (p.out_f32 && (p.conv || p.res || p.act != MOPAR_ACT_NONE || p.N % 8 != 0 || p.ldc % 8 != 0)) return false;
+    if (p.bias2 && !p.out_f32) return false;
+    // a 64-wide k tile of a conv lies in one tap, and a tap has a bit of a 32-bit mask; the operand and
+    // the rows of padding before it are addressed together
+    if (p.conv && (p.cs % 64 != 0 || p.kh * p.kw > 32 || p.pad >= p.img_w ||
+                   int64_t(p.a_bytes) + (int64_t(p.pad) * p.img_w + p.pad) * p.cs * 2 >= (int64_t(1) << 31)))
+        return false;
+    const int64_t tiles = ((p.M + kPPTile - 1) / kPPTile) * ((p.N + kPPTile - 1) / kPPTile);
+    const int64_t rounds = (tiles + kCUs - 1) / kCUs;
+    return p.K >= 256 && p.N >= 192 && (rounds == 1 ? tiles >= 140 : tiles * 10 >= rounds * kCUs * 6);
+}
+
+static hipError_t launch_pp(const GemmParams& params, hipStream_t st) {
     GemmParams p = params;
     p.c_bytes = static_cast<uint32_t>(((p.M - 1) * p.ldc + p.N) * (p.out_f32 ? 4 : 2));
-    const int64_t mt = (p.M + 255) / 256, nt = (width + 255) / 256;
-    const int64_t total = mt * nt * p.ksub;
-    if (total >= (int64_t(1) << 31) / kWideGroupM) return hipErrorInvalidValue;
+    const int64_t mt = (p.M + kPPTile - 1) / kPPTile, nt = (p.N + kPPTile - 1) / kPPTile;
+    const int64_t total = mt * nt;
+    if (total >= (int64_t(1) << 31) / kPPGroupM) return hipErrorInvalidValue;
     p.g_mt = static_cast<int>(mt);
     p.g_nt = static_cast<int>(nt);
     p.g_total = static_cast<int>(total);
     p.g_per_xcd = static_cast<int>((total + 7) / 8);
-    p.g_cols = static_cast<int>(nt * p.ksub);
     p.g_nk = (p.K + 63) / 64;
-    p.g_q = p.N / p.ksub;
-    p.g_rr = p.N % p.ksub;
-    p.g_div_group = FastDiv(static_cast<unsigned>(kWideGroupM * p.g_cols));
-    const int last = static_cast<int>(mt - (mt - 1) / kWideGroupM * kWideGroupM);
+    p.g_div_group = FastDiv(static_cast<unsigned>(kPPGroupM * p.g_nt));
+    const int last = static_cast<int>(mt - (mt - 1) / kPPGroupM * kPPGroupM);
     p.g_div_last = FastDiv(static_cast<unsigned>(last));
-    p.g_div_nt = FastDiv(static_cast<unsigned>(nt));
-    if (p.wide_ctr && !p.res && p.act == MOPAR_ACT_NONE) {
-        // persistent: one block per CU, tiles from per-XCD counters zeroed here
-        if (p.g_nk < 2) return hipErrorInvalidValue;
-        const hipError_t e = launch_fill_zero(p.wide_ctr, kWideCtrBytes, st);
-        if (e != hipSuccess) return e;
-        launch_kernel(gemm_wide_persistent, dim3(static_cast<unsigned>(kCUs)), dim3(256), 0, st, p);
-        return hipGetLastError();
-    }
-    const int64_t grid = (total + 7) / 8 * 8;
-    launch_kernel(gemm_wide_kernel<kWideBStages>, dim3(static_cast<unsigned>(grid)), dim3(256), 0, st, p);
+    if (p.g_nk < 2) return hipErrorInvalidValue;
+    // tiles per block: one round of 32 blocks per XCD where that is at most kPPChunk tiles each
+    const int rounds = (p.g_per_xcd + 31) / 32;
+    p.g_chunk = rounds < kPPChunk ? rounds : kPPChunk;
+    const int per = 32 * p.g_chunk;
+    const unsigned grid = static_cast<unsigned>((p.g_per_xcd + per - 1) / per * 32 * 8);
+    // whole aligned groups of eight columns everywhere
+    const bool regular = p.N % 8 == 0 && p.ldc % 8 == 0 &&
+                         ((reinterpret_cast<uintptr_t>(p.C) | reinterpret_cast<uintptr_t>(p.res) |
+                           reinterpret_cast<uintptr_t>(p.bias) | reinterpret_cast<uintptr_t>(p.bias2)) & 15) == 0;
+    if (p.out_f32 && (!regular || p.conv)) return hipErrorInvalidValue;   // not in pp_class
+    const dim3 g(grid), b(512);
+    auto go_act = [&](auto conv, auto epi) {
+        constexpr bool C = decltype(conv)::value;
+        constexpr int E = decltype(epi)::value;
+        if (p.act == MOPAR_ACT_RELU)
+            launch_kernel(gemm_pp_kernel<C, E, MOPAR_ACT_RELU>, g, b, 0, st, p);
+        else if (p.act == MOPAR_ACT_GELU)
+            launch_kernel(gemm_pp_kernel<C, E, MOPAR_ACT_GELU>, g, b, 0, st, p);
+        else
+            launch_kernel(gemm_pp_kernel<C, E, MOPAR_ACT_NONE>, g, b, 0, st, p);
+    };
+    auto go = [&](auto conv) {
+        constexpr bool C = decltype(conv)::value;
+        if (!regular)
+            go_act(conv, std::integral_constant<int, PP_ANY>{});
+        else if (p.out_f32)
+            launch_kernel(gemm_pp_kernel<false, PP_F32, MOPAR_ACT_NONE>, g, b, 0, st, p);
+        else if (p.res)
+            go_act(conv, std::integral_constant<int, PP_RES>{});
+        else
+            go_act(conv, std::integral_constant<int, PP_BF16>{});
+    };
+    if (p.conv)
+        go(std::true_type{});
+    else
+        go(std::false_type{});
     return hipGetLastError();
-}
-
-// Whether an operator runs on gemm_wide_kernel (and so on the 32 x 32 x 16 MFMA): dense bf16
-// with the standard epilogue, not a boundary codec layer, K of at least 256, and at least four
-// rounds of 256 x 256 tiles over the whole (M, N) -- with fewer, the block's unhidden set-up and
-// epilogue cost more than its faster K loop saves (measured).  A function of the operator's
-// (M, N, K) alone, never of the sub-slice count, so all its sub-slice launches take the same path.
-static bool wide_class(const GemmParams& p) {
-    // (the output span is addressed with 32-bit offsets, below the out-of-range offset 2^31)
-    const int64_t c_span = ((p.M - 1) * p.ldc + p.N) * (p.out_f32 ? 4 : 2);
-    return !p.conv && !p.thin && p.epi == EPI_STD && p.splits == 1 && p.K >= 256 && p.M >= 512 && p.N >= 512 &&
-           ((p.M + 255) / 256) * ((p.N + 255) / 256) >= 4 * kCUs && c_span < (int64_t(1) << 31);
 }
 
 template <typename T>
 static hipError_t dispatch(const GemmParams& p, hipStream_t st) {
     const int width = (p.N + p.ksub - 1) / p.ksub;   // widest sub-slice
     if constexpr (sizeof(T) == 2) {
-        if (wide_class(p)) return launch_wide(p, width, st);
+        if (pp_class(p)) return launch_pp(p, st);
     }
     // few rows: the four waves split K (four 64-wide sub-stages per stage) instead of the tile
     if (p.M <= 16) return launch_cfg<T, 16, 64, 1, 1, 3, 4, 4>(p, width, st);

@@ -119,12 +119,10 @@ struct GemmParams {
     // patch-staged 3x3 conv: spatial tiles per image and per tile row, and their divisors
     int h_tiles, h_tx;
     FastDiv h_div_tiles, h_div_tx;
-    // 256 x 256 tiles: kWideCtrBytes of tile counters (optional; with them the launch is
-    // persistent), and the output span in bytes (set by the launcher)
-    unsigned* wide_ctr;
+    // 256 x 256 tiles: the output span in bytes and the tiles per block (set by the launcher)
     uint32_t c_bytes;
+    int g_chunk;
 };
-constexpr size_t kWideCtrBytes = 256;
 
 // Split-K factor used for an (M, N, K) product.  A function of the shape
 // only -- never of the sub-slice count -- so sub-sliced launches reduce in

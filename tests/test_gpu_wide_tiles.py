@@ -1,0 +1,46 @@
+"""The 256 x 256 tile kernel at its edges: remainders of M, N and K, widths off the 8-column group,
+several tiles per block, conv taps at image borders, residuals and activations -- against the
+oracle (bf16 tolerance of the parity tests) and, sub-sliced, bit for bit against the unsplit launch."""
+import pytest
+import torch
+
+import oracle
+import synth
+from tests.helpers import TOL, rel_err
+from tests.test_gpu_parity import P, _np, conv_model, run_gpu, seq_ids, seq_input_model
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,k,n,act,res,ksub", [
+    (8961, 264, 1000, "gelu", False, 3),     # 36 x 4 tiles: one row, 232 columns and 8 of k in the last ones
+    (8961, 320, 1001, "relu", True, 4),      # rows at odd addresses, a last group of one column, residual
+    (8960, 256, 1022, "none", False, 2),     # a last group of six columns
+    (20001, 256, 1000, "none", True, 8),     # 79 x 4 tiles: two per block, residual
+    (20001, 296, 1004, "gelu", True, 1),     # the same off the group, a last group of four columns
+])
+def test_linear_edges(m, k, n, act, res, ksub):
+    bld, x = seq_input_model("bf16", 1, m, k)
+    r = bld.linear(x, n, "none", "r", "rand") if res else None
+    y = bld.linear(x, n, act, "lin", "rand", res=r, rd=True)
+    mod = bld.finish(y, 1)
+    ids = seq_ids(1, m)
+    y1, _, _ = run_gpu(mod, ids, P.make_plan(1, [0], [1]))
+    assert rel_err(_np(y1), oracle.forward(mod, ids)) <= TOL["bf16"]
+    yk, _, _ = run_gpu(mod, ids, P.make_plan(1, [0], [ksub]))
+    assert torch.equal(yk, y1)
+
+
+@pytest.mark.parametrize("n,c,hw,cout,k,stride,pad,residual", [
+    (9, 64, 63, 200, 3, 1, 1, False),        # 140 tiles, 200 of 256 columns, borders on every side
+    (10, 128, 61, 201, 3, 1, 1, True),       # odd width with a residual
+    (9, 64, 126, 192, 3, 2, 1, False),       # strided
+    (9, 64, 63, 192, 5, 1, 2, False),        # 25 taps, two pixels of padding
+])
+def test_conv_edges(n, c, hw, cout, k, stride, pad, residual):
+    mod = conv_model("bf16", n, c, hw, cout, k, stride, pad, residual=residual, pre=True)
+    x = synth.random_tensor((n, c, hw, hw), "f32", seed=11)
+    y1, _, _ = run_gpu(mod, x, P.make_plan(1, [0], [1]))
+    assert rel_err(_np(y1), oracle.forward(mod, x)) <= TOL["bf16"]
+    yk, _, _ = run_gpu(mod, x, P.make_plan(1, [0], [3]))
+    assert torch.equal(yk, y1)
