@@ -481,55 +481,117 @@ hipError_t launch_embed(const int32_t* ids, const void* table, void* y, int64_t 
 }
 
 // ---------------------------------------------------------------------------
-// Multi-head self-attention, head dim 64, seq <= 128.  One block per (b, h):
-// K and V of the head staged in LDS as fp32; one thread per query row runs
-// the softmax online (running max and normaliser) and accumulates P.V in
-// registers.  Scores and probabilities never leave registers.
+// float32 attention on the matrix cores (v_mfma_f32_16x16x4_f32), head dim 64, seq <= 128.  One block
+// per (batch, head, 64-query tile), a wave per 16 queries; K and V of the head sit in LDS as float32.
+// The k index of an MFMA may run over its operands' elements in any order that both share, so the
+// fragments are whole 16-byte reads: S^T = K Q^T takes dim 16 g + s in step s for lane group g = lane / 16,
+// O^T = V^T P^T key 16 t + 4 g + e in step (t, e), which is where S^T left the probabilities of that key --
+// they stay in registers -- and row i of its dim tile d stands for dim 4 i + d.  Every product and sum is
+// float32, the softmax runs over all keys at once, keys past seq have probability 0 (their V rows are
+// zero).  4 x 77 tokens, 12 heads: 64.6 us as one thread per query row on the vector ALUs, 8.6 us here (the
+// MFMAs of a block take 2.2 us).
 // ---------------------------------------------------------------------------
 constexpr int ATT_D = 64;
 constexpr int ATT_MAXS = 128;
+constexpr int ATT_LD = ATT_D + 4;          // float row stride: neighbouring rows start 4 banks apart
 
-template <typename T>
-__global__ __launch_bounds__(ATT_MAXS) void attention_kernel(const T* __restrict__ qkv, T* __restrict__ y, int seq,
-                                                             int heads, float scale) {
-    __shared__ float ks[ATT_MAXS][ATT_D];   // read as broadcasts: no padding needed
-    __shared__ float vs[ATT_MAXS][ATT_D];
-    const int b = blockIdx.x / heads, h = blockIdx.x % heads;
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+__global__ __launch_bounds__(256) void attention_f32_kernel(const float* __restrict__ qkv, float* __restrict__ y, int seq,
+                                                            int heads, float scale) {
+    __shared__ __attribute__((aligned(16))) float ks[ATT_MAXS * ATT_LD];
+    __shared__ __attribute__((aligned(16))) float vs[ATT_MAXS * ATT_LD];
+    constexpr int NT = ATT_MAXS / 16;
+    const int qtiles = (seq + 63) / 64;
+    const int qt = blockIdx.x % qtiles, bh = blockIdx.x / qtiles, b = bh / heads, h = bh % heads;
     const int f = heads * ATT_D;
-    const T* base = qkv + static_cast<int64_t>(b) * seq * 3 * f;
-    for (int idx = threadIdx.x; idx < seq * ATT_D; idx += blockDim.x) {
-        const int r = idx / ATT_D, e = idx % ATT_D;
-        ks[r][e] = to_f(base[static_cast<int64_t>(r) * 3 * f + f + h * ATT_D + e]);
-        vs[r][e] = to_f(base[static_cast<int64_t>(r) * 3 * f + 2 * f + h * ATT_D + e]);
+    const int64_t row3 = 3 * static_cast<int64_t>(f);
+    const float* base = qkv + static_cast<int64_t>(b) * seq * row3 + h * ATT_D;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lr = lane & 15, g = lane >> 4;
+    const int nt = (seq + 15) / 16;            // key tiles
+    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+
+    // this lane's query row, dims 16 g .. 16 g + 15 (a row past seq reads the last one; it is not stored)
+    const int q = qt * 64 + wave * 16 + lr;
+    const float* qr = base + static_cast<int64_t>(min(q, seq - 1)) * row3 + 16 * g;
+    f32x4_t qf[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) qf[i] = *reinterpret_cast<const f32x4_t*>(qr + 4 * i);
+    // K and V rows, 16 bytes a thread, up to the last key tile's end (zeros past seq)
+    for (int i0 = 0; i0 < nt * 16 * 16; i0 += 4 * 256) {
+        f32x4_t kv[4], vv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * 256 + threadIdx.x, r = min(i >> 4, seq - 1);
+            const float* src = base + static_cast<int64_t>(r) * row3 + f + (i & 15) * 4;
+            kv[u] = *reinterpret_cast<const f32x4_t*>(src);
+            vv[u] = *reinterpret_cast<const f32x4_t*>(src + f);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * 256 + threadIdx.x, r = i >> 4;
+            if (r < nt * 16) {
+                *reinterpret_cast<f32x4_t*>(ks + r * ATT_LD + (i & 15) * 4) = r < seq ? kv[u] : zero;
+                *reinterpret_cast<f32x4_t*>(vs + r * ATT_LD + (i & 15) * 4) = r < seq ? vv[u] : zero;
+            }
+        }
     }
     __syncthreads();
-    const int i = threadIdx.x;
-    if (i >= seq) return;
-    float q[ATT_D], o[ATT_D];
-    const T* qr = base + static_cast<int64_t>(i) * 3 * f + h * ATT_D;
+    if (qt * 64 + wave * 16 >= seq) return;    // (no barrier follows)
+
+    // S^T: this lane ends with keys 16 t + 4 g + e of query lr
+    f32x4_t s[NT];
 #pragma unroll
-    for (int e = 0; e < ATT_D; ++e) {
-        q[e] = to_f(qr[e]);
-        o[e] = 0.0f;
+    for (int t = 0; t < NT; ++t) {
+        s[t] = zero;
+        if (t >= nt) continue;
+        const float* kr = ks + (t * 16 + lr) * ATT_LD + 16 * g;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const f32x4_t kf = *reinterpret_cast<const f32x4_t*>(kr + 4 * i);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[e], qf[i][e], s[t], 0, 0, 0);
+        }
     }
-    float mx = -INFINITY, den = 0.0f;
-    for (int jj = 0; jj < seq; ++jj) {
-        float sc = 0.0f;
+    float mx = -INFINITY;
 #pragma unroll
-        for (int e = 0; e < ATT_D; ++e) sc += q[e] * ks[jj][e];
-        sc *= scale;
-        const float mnew = fmaxf(mx, sc);
-        const float corr = __expf(mx - mnew);
-        const float pj = __expf(sc - mnew);
-        den = den * corr + pj;
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int e = 0; e < ATT_D; ++e) o[e] = o[e] * corr + pj * vs[jj][e];
-        mx = mnew;
+        for (int e = 0; e < 4; ++e) {
+            s[t][e] *= scale;
+            if (t * 16 + 4 * g + e < seq) mx = fmaxf(mx, s[t][e]);
+        }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    float sum = 0.0f;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            s[t][e] = t * 16 + 4 * g + e < seq ? __expf(s[t][e] - mx) : 0.0f;
+            sum += s[t][e];
+        }
+    sum += __shfl_xor(sum, 16, 64);
+    sum += __shfl_xor(sum, 32, 64);
+    // O^T: this lane ends with dims 16 g + 4 e + d of query lr
+    f32x4_t o[4] = {zero, zero, zero, zero};
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        if (t >= nt) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const f32x4_t vf = *reinterpret_cast<const f32x4_t*>(vs + (t * 16 + 4 * g + e) * ATT_LD + 4 * lr);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) o[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[d], s[t][e], o[d], 0, 0, 0);
+        }
     }
-    const float inv = 1.0f / den;
-    T* yr = y + (static_cast<int64_t>(b) * seq + i) * f + h * ATT_D;
+    if (q >= seq) return;
+    const float inv = 1.0f / sum;
+    float* out = y + (static_cast<int64_t>(b) * seq + q) * f + h * ATT_D + 16 * g;
 #pragma unroll
-    for (int e = 0; e < ATT_D; ++e) yr[e] = from_f<T>(o[e] * inv);
+    for (int e = 0; e < 4; ++e)
+        *reinterpret_cast<f32x4_t*>(out + 4 * e) = f32x4_t{o[0][e] * inv, o[1][e] * inv, o[2][e] * inv, o[3][e] * inv};
 }
 
 // ---------------------------------------------------------------------------
@@ -549,7 +611,6 @@ constexpr int AM_LD = AM_D + 8;     // bf16 row stride of Q and K (144 bytes)
 constexpr int AM_LP = AM_K + 8;     // bf16 row stride of V^T and P (272 bytes)
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ bf16x8_t lds8(const __bf16* p) { return *reinterpret_cast<const bf16x8_t*>(p); }
 
@@ -685,7 +746,7 @@ hipError_t launch_attention(const void* qkv, void* y, int batch, int seq, int he
         launch_kernel(attention_mfma_kernel, dim3((n_tiles + 7) / 8 * 8), dim3(256), 0, s,
                       static_cast<const __bf16*>(qkv), static_cast<__bf16*>(y), seq, heads, scale, n_tiles);
     } else {
-        launch_kernel(attention_kernel<float>, dim3(batch * heads), dim3(ATT_MAXS), 0, s,
+        launch_kernel(attention_f32_kernel, dim3(batch * heads * ((seq + 63) / 64)), dim3(256), 0, s,
                       static_cast<const float*>(qkv), static_cast<float*>(y), seq, heads, scale);
     }
     return hipGetLastError();
