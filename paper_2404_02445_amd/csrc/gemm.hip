@@ -644,9 +644,30 @@ __global__ __launch_bounds__(WM * WN * KS * 64) void gemm_kernel(const GemmParam
             }
     };
 
+    // float32 sums in blocks of 128 of k (64 per wave where the waves split K), added up in order: a rounding
+    // error that grows with the number of blocks plus the length of one instead of with K (a float32
+    // BERT-base layer on 4 x 77 tokens: 7.0e-7 of the result without, 3.2e-7 with, 5.0e-7 with the K
+    // splits that kept the sums short before)
+    constexpr bool BLOCKED = sizeof(T) == 4;
+    f32x4 total[BLOCKED ? FM : 1][BLOCKED ? FN : 1];
+    if constexpr (BLOCKED) {
+#pragma unroll
+        for (int a = 0; a < FM; ++a)
+#pragma unroll
+            for (int b = 0; b < FN; ++b) total[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    auto flush = [&]() {
+        if constexpr (BLOCKED) {
+#pragma unroll
+            for (int a = 0; a < FM; ++a)
+#pragma unroll
+                for (int b = 0; b < FN; ++b) total[a][b] += acc[a][b], acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
     for (int st = 0; st < nst; ++st) {
         const int buf = st % NS;
         const int later = min(NS - 2, nst - 1 - st);   // stages issued after this one
+        if (BLOCKED && st > 0 && st % (KS == 1 ? 4 : 2) == 0) flush();
         wait_stages<LMIN * KH>(later);                 // this wave's share of stage st has landed
         __builtin_amdgcn_s_barrier();                  // every wave's share has; stage st-1 fully consumed
         if (st + NS - 1 < nst) issue_stage(st + NS - 1, (st + NS - 1) % NS);
@@ -694,6 +715,14 @@ __global__ __launch_bounds__(WM * WN * KS * 64) void gemm_kernel(const GemmParam
 #pragma unroll
         for (int b = 0; b < FN; ++b) pin(b1[b]);
         mfmas(a1, b1);
+    }
+
+    if constexpr (BLOCKED) {
+        flush();
+#pragma unroll
+        for (int a = 0; a < FM; ++a)
+#pragma unroll
+            for (int b = 0; b < FN; ++b) acc[a][b] = total[a][b];
     }
 
     // --- epilogue --------------------------------------------------------------------------
@@ -1059,13 +1088,13 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
     }
     u32x4 af[2][4], bf[2][4];
     f32x16 acc[2][2][2];                       // [A half][row tile][B half]
-    bool stored = false;                       // the block has stored a tile, 16 stores or more a wave
+    bool stored = false;                       // the block has stored a tile, with a known number of stores per wave
     // An MFMA step, after the reads and loads of its memory step: wait for the reads and for the loads
     // that the next memory step reads, the eight issued since staying in flight (in a tile's first
-    // k tile the previous tile's 16 stores, or more, lie between them)
+    // k tile the previous tile's 16 stores, 32 of float32 results, lie between them)
     auto mfma_step = [&](auto i, auto first) __attribute__((always_inline)) {
         if (decltype(first)::value && stored)
-            asm volatile("s_waitcnt vmcnt(24) lgkmcnt(0)" ::: "memory");
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(EPI == PP_F32 ? 40 : 24) : "memory");
         else
             asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
 #pragma unroll
@@ -1596,8 +1625,13 @@ int gemm_splits(int64_t M, int N, int K, int dtype, int epi) {
     const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);   // reference tiling, independent of k
     // the reduce pass costs about as much as a dozen k stages: split only long K loops
     if (nk < 24) return 1;
+    // (float32 is MFMA-bound: up to 32 stages, 1024 of k, the loop costs less than the reduce pass saves,
+    // and a doubling that leaves the CU with the most tiles as much work only adds that pass.  308 x 768 ->
+    // 2304, 180 tiles: 24.7 us with two splits, 20.4 us with one)
+    if (dtype != MOPAR_BF16 && nk <= 32) return 1;
+    auto load = [&](int64_t sp) { return (tiles * sp + kCUs - 1) / kCUs * 16 / sp; };
     int s = 1;
-    while (s < 16 && tiles * s < kCUs && nk / (2 * s) >= 4) s *= 2;
+    while (s < 16 && tiles * s < kCUs && nk / (2 * s) >= 4 && (dtype == MOPAR_BF16 || load(2 * s) < load(s))) s *= 2;
     return s;
 }
 
@@ -1725,11 +1759,19 @@ static hipError_t dispatch(const GemmParams& p, hipStream_t st) {
     if constexpr (sizeof(T) == 2) {
         if (pp_class(p)) return launch_pp(p, st);
     }
+    // float32 products of at most 16 64 x 64 tiles (a batch-1 CNN's later convs and its classifier): the MFMA time
+    // of a block and its serial K loop both count, so small tiles and K split over the waves
+    if (sizeof(T) == 4 && p.epi == EPI_STD && ((p.M + 63) / 64) * ((p.N + 63) / 64) <= 16)
+        return launch_cfg<T, 32, 16, 1, 1, 2, 4, 4>(p, width, st);
     // few rows: the four waves split K (four 64-wide sub-stages per stage) instead of the tile
     if (p.M <= 16) return launch_cfg<T, 16, 64, 1, 1, 3, 4, 4>(p, width, st);
     // the LSTM step: 32 x 16 tiles (twice the blocks of 64 x 16, less LDS each) measured
     // fastest, alone and beside other streams' kernels
     if (p.epi == EPI_LSTM) return launch_cfg<T, 32, 16, 1, 1, 2, 4, 4>(p, width, st);
+    // few blocks of 64 x 64: eight times as many of 32 x 16 (BERT-base's layer on 60 tokens 47.9 -> 40.2 us, a
+    // 49-pixel bottleneck of ResNet-50's last stage 28 -> 25 us, 33 x 6400 -> 1024 -> 1024 -> 1000 29 -> 22.6 us)
+    if (p.M <= 64 && (p.M + 63) / 64 * ((width + 63) / 64) * p.ksub * p.splits < kCUs / 2)
+        return launch_cfg<T, 32, 16, 1, 1, 2, 4, 4>(p, width, st);
     if (p.M <= 64) {
         if (width >= 64) return launch_cfg<T, 64, 64, 1, 1, 2, 4, 4>(p, width, st);
         return launch_cfg<T, 64, 16, 1, 1, 3, 4, 4>(p, width, st);
@@ -1740,6 +1782,9 @@ static hipError_t dispatch(const GemmParams& p, hipStream_t st) {
     // compute unit a block: 32 x 32 tiles (measured about 20 % faster on such encoders, cold)
     if (p.thin && width <= 128 && blocks((p.M + 63) / 64, width >= 64 ? 64 : 32) < kCUs)
         return launch_cfg<T, 32, 32, 2, 2, 4>(p, width, st);
+    // float32 is MFMA-bound, rows past M cost as much as any: 64-row tiles where 128-row ones would leave more
+    // than a tenth of theirs empty (308 x 768 -> 3072: 32.6 us on 128 x 64 tiles, 21.7 us on 64 x 64)
+    if (sizeof(T) == 4 && width >= 64 && mt * 128 * 10 > p.M * 11) return launch_cfg<T, 64, 64, 2, 4, 4>(p, width, st);
     // 128-wide tiles unless they would leave more than a tenth of the columns they cover empty
     const bool w128 = width >= 128 && (width + 127) / 128 * 128 * 10 <= width * 11;
     if (w128 && blocks(mt, 128) >= kCUs) return launch_cfg<T, 128, 128, 2, 4, 2>(p, width, st);
