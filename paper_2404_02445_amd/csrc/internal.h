@@ -153,6 +153,12 @@ inline bool gemm_operands_fit(int64_t a_bytes, int64_t b_bytes) {
 // NCHW float32 -> NHWC (model dtype), channels padded with zeros to cs.
 hipError_t launch_nchw_to_nhwc(const float* x, void* y, int n, int c, int h, int w, int cs, int dtype,
                                hipStream_t s);
+// First-layer 7x7 stride-2 conv of an NCHW float32 image (at most four channels) with bf16 results: whether
+// an op qualifies, and its launch; with `pool` the 3x3, stride-2, padding-1 max pool of its results
+// ([n][ph][pw][ldc]) is written instead of them.
+bool stem_ok(int dtype, int c, int kh, int kw, int stride, int cout, int64_t ldc, int64_t out_off, int act, bool res);
+hipError_t launch_stem(const float* x, const void* w, const void* b, void* y, int n, int c, int h, int wd, int pad, int ch,
+                       int cw, int ph, int pw, int cout, int64_t ldc, int act, bool pool, hipStream_t s);
 hipError_t launch_maxpool(const void* x, void* y, int n, int h, int w, int c, int k, int stride, int pad,
                           int ho, int wo, int dtype, hipStream_t s);
 hipError_t launch_avgpool(const void* x, void* y, int n, int hw, int c, int dtype, hipStream_t s);

@@ -847,6 +847,253 @@ hipError_t launch_codec_narrow(const void* x, const void* w, const void* b, void
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// First-layer 7x7, stride-2 convolution of an NCHW float32 image of at most four channels (gfx950, bf16
+// results), with the 3x3, stride-2, padding-1 max pool that follows it in the same pass.
+//
+// As three passes (a channels-last bf16 copy, an implicit GEMM, the pool) the layer reads and writes
+// its 112 x 112 x 64 activation through memory, and the GEMM works on K = 7 x 7 x 8 with 245 of 392
+// products on padding channels.  Here a block owns an 8 x 8 tile of pooled pixels (without the pool a
+// 16 x 16 tile of conv pixels) and 64 output channels: the input patch goes to LDS once as bf16,
+// four channels a pixel, and the contraction runs over k = (tap row r, tap column 0..7, channel 0..3),
+// 32 wide per tap row with the eighth column's weights zero.  The eight k values of an MFMA
+// fragment lane are two neighbouring pixels of the patch: one aligned 16-byte LDS read, no im2col.
+// Each wave keeps the weights of its 32 channels in registers (14 fragments) and takes every other
+// 16-pixel row tile.  The conv tile is rounded to bf16 in LDS, as the unfused op stores it, and pooled
+// there, so the results equal the conv followed by the pool bit for bit.  The conv pixels on tile
+// borders are computed twice (289 for 256).
+//
+// ResNet-50's stem at batch 32 (224 x 224): 75 us as three kernels, 36 us here; at batch 8 33.6 -> 11.5 us.
+// It is bound by the latency of a block's phases (patch, weights, MFMAs, pool) with three blocks per
+// CU: 1568 blocks in two rounds.  Loads under branches cost most of it before they went through buffer
+// resources (52 us), weights read in fragment order 3 us more.
+// ---------------------------------------------------------------------------
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int STEM_K = 7;                    // window
+constexpr int STEM_LD = 64 + 8;              // bf16 row stride of the conv tile in LDS (spreads rows over the banks)
+
+struct StemParams {
+    const float* x;      // [n][c][h][w]
+    const __bf16* w;     // [cout][7][7][8], channels past c zero
+    const __bf16* b;     // [cout] or null
+    __bf16* y;           // POOL: [n][ph][pw][ldc], else [n][ch][cw][ldc]
+    int c, h, wd, pad;
+    int ch, cw;          // conv output
+    int ph, pw;          // pool output
+    int cout, ldc, act;
+    int tiles, tx;       // tiles per image, per tile row
+};
+
+__device__ __forceinline__ float act_of(float v, int act) {
+    if (act == MOPAR_ACT_RELU) return v > 0.0f ? v : 0.0f;
+    return v;
+}
+__device__ __forceinline__ float bf_lo(unsigned w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf_hi(unsigned w) { return __uint_as_float(w & 0xffff0000u); }
+
+constexpr unsigned kOOB = 0x80000000u;   // past every resource here
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* base, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), static_cast<short>(0), static_cast<int>(bytes), 0x00020000);
+}
+
+template <bool POOL>
+__global__ __launch_bounds__(256) void stem_kernel(const StemParams p) {
+    constexpr int TC = POOL ? 17 : 16;           // conv tile edge
+    constexpr int NPIX = TC * TC, MT = (NPIX + 15) / 16;
+    constexpr int PR = 2 * (TC - 1) + STEM_K;        // patch rows
+    constexpr int PW = 2 * (TC - 1) + STEM_K + 1;    // patch columns (even; the last one meets zero weights)
+    constexpr int PPIX = PR * PW, LPT = (PPIX + 255) / 256;
+    __shared__ __attribute__((aligned(16))) u32x2 patch[PPIX];
+    // the conv tile; before it, the 64 channels' weights as [channel][tap row][8 columns][4 channels]
+    __shared__ __attribute__((aligned(16))) __bf16 conv[NPIX * STEM_LD];
+    static_assert(sizeof(conv) >= 64 * STEM_K * 8 * sizeof(u32x2), "weights fit where the conv tile goes");
+    u32x2* const wl = reinterpret_cast<u32x2*>(conv);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int img = blockIdx.x / p.tiles, t = blockIdx.x - img * p.tiles;
+    const int ty = t / p.tx, tx = t - ty * p.tx;
+    const int n0 = blockIdx.y * 64;
+    // first conv pixel of the tile (with the pool, its window's corner: -1 at the image's edge)
+    const int cy0 = POOL ? 16 * ty - 1 : 16 * ty, cx0 = POOL ? 16 * tx - 1 : 16 * tx;
+    const int iy0 = 2 * cy0 - p.pad, ix0 = 2 * cx0 - p.pad;
+
+    // the patch: all loads of a thread go out together, then the conversions (zeros outside the image)
+    // (through a buffer resource: an offset past it reads zeros, where a branch around each load would make
+    // every load wait for the one before it)
+    const unsigned plane = static_cast<unsigned>(p.h) * static_cast<unsigned>(p.wd);
+    const auto xr = rsrc(p.x + static_cast<int64_t>(img) * p.c * plane, static_cast<unsigned>(p.c) * plane * 4u);
+    float v[LPT][4];
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) {
+        const int q = tid + 256 * i, r = q / PW, cc = q - r * PW;
+        const int iy = iy0 + r, ix = ix0 + cc;
+        const bool in = q < PPIX && static_cast<unsigned>(iy) < static_cast<unsigned>(p.h) &&
+                        static_cast<unsigned>(ix) < static_cast<unsigned>(p.wd);
+        const unsigned off = in ? static_cast<unsigned>(iy * p.wd + ix) * 4u : kOOB;
+#pragma unroll
+        for (int ch = 0; ch < 4; ++ch)           // (the scalar offset is not part of the range check)
+            v[i][ch] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, static_cast<int>(ch < p.c ? off : kOOB),
+                                                                                      static_cast<int>(ch * plane * 4u), 0));
+    }
+
+    // the weights of channels n0 .. n0 + 63, first four channels of each tap: whole lines of the (contiguous)
+    // weight rows (fragments read straight from memory touch 16 rows per load: 3 us per block)
+    constexpr int WPT = (64 * STEM_K * STEM_K + 255) / 256;
+    u32x2 wv[WPT];
+    const int wmax = (p.cout - n0) * (STEM_K * STEM_K) - 1;
+#pragma unroll
+    for (int i = 0; i < WPT; ++i) {
+        const int q = min(min(tid + 256 * i, 64 * STEM_K * STEM_K - 1), wmax);
+        wv[i] = *reinterpret_cast<const u32x2*>(p.w + (static_cast<int64_t>(n0) * STEM_K * STEM_K + q) * 8);
+    }
+    const int wn = wave & 1, wm = wave >> 1;
+    const auto br = rsrc(p.b, p.b ? static_cast<unsigned>(p.cout) * 2u : 0u);
+    float bias[2][4];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int n = n0 + wn * 32 + j * 16 + (lane >> 4) * 4 + e;
+            bias[j][e] = bf_lo(static_cast<unsigned short>(
+                __builtin_amdgcn_raw_buffer_load_b16(br, n < p.cout ? 2 * n : static_cast<int>(kOOB), 0, 0)));
+        }
+
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) {
+        const int q = tid + 256 * i;
+        if (q < PPIX)
+            patch[q] = __builtin_bit_cast(u32x2, bf16x4{(__bf16)v[i][0], (__bf16)v[i][1], (__bf16)v[i][2], (__bf16)v[i][3]});
+    }
+#pragma unroll
+    for (int i = 0; i < WPT; ++i) {
+        const int q = tid + 256 * i, n = q / (STEM_K * STEM_K), rc = q - n * (STEM_K * STEM_K), r = rc / STEM_K;
+        if (q < 64 * STEM_K * STEM_K) wl[(n * STEM_K + r) * 8 + rc - r * STEM_K] = wv[i];
+    }
+    for (int q = tid; q < 64 * STEM_K; q += 256) wl[q * 8 + 7] = u32x2{0u, 0u};
+    __syncthreads();
+    // this wave's weights: channels n0 + 32 wn + 16 j + l % 16, k of tap row r: columns 2 (l / 16) and + 1
+    u32x4 wf[2][STEM_K];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < STEM_K; ++r)
+            wf[j][r] = *reinterpret_cast<const u32x4*>(wl + ((wn * 32 + j * 16 + (lane & 15)) * STEM_K + r) * 8 + 2 * (lane >> 4));
+    __syncthreads();
+
+    // conv pixels 16 mt + l % 16 (past the tile: the last one again), weight fragment first: a lane ends
+    // with four consecutive channels of one pixel; the next row tile's fragments are read under the MFMAs
+    auto read = [&](int mt, u32x4 (&af)[STEM_K]) {
+        const int px = min(mt * 16 + (lane & 15), NPIX - 1), oy = px / TC, ox = px - oy * TC;
+        const u32x2* src = patch + (2 * oy) * PW + 2 * ox + 2 * (lane >> 4);
+#pragma unroll
+        for (int r = 0; r < STEM_K; ++r) af[r] = *reinterpret_cast<const u32x4*>(src + r * PW);
+    };
+    auto compute = [&](int mt, u32x4 (&af)[STEM_K]) {
+        f32x4 acc[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[j] = f32x4{bias[j][0], bias[j][1], bias[j][2], bias[j][3]};
+#pragma unroll
+        for (int r = 0; r < STEM_K; ++r)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[j][r]),
+                                                                 __builtin_bit_cast(bf16x8, af[r]), acc[j], 0, 0, 0);
+        const int px = mt * 16 + (lane & 15);
+        if (px >= NPIX) return;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (__bf16)act_of(acc[j][e], p.act);
+            *reinterpret_cast<bf16x4*>(&conv[px * STEM_LD + wn * 32 + j * 16 + (lane >> 4) * 4]) = o;
+        }
+    };
+    u32x4 a0[STEM_K], a1[STEM_K];
+    read(wm, a0);
+    for (int mt = wm; mt < MT; mt += 4) {
+        if (mt + 2 < MT) read(mt + 2, a1);
+        compute(mt, a0);
+        if (mt + 2 >= MT) break;
+        if (mt + 4 < MT) read(mt + 4, a0);
+        compute(mt + 2, a1);
+    }
+    __syncthreads();
+
+    if constexpr (POOL) {
+        // 64 pooled pixels x 8 chunks of 8 channels; window pixels outside the conv's output are skipped
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int q = tid + 256 * i, chunk = q & 7, pix = q >> 3, py = pix >> 3, px = pix & 7;
+            const int oy = 8 * ty + py, ox = 8 * tx + px, n = n0 + chunk * 8;
+            if (oy >= p.ph || ox >= p.pw || n >= p.cout) continue;
+            float m[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) m[e] = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const int ly = 2 * py + r, lx = 2 * px + c;
+                    const bool in = static_cast<unsigned>(cy0 + ly) < static_cast<unsigned>(p.ch) &&
+                                    static_cast<unsigned>(cx0 + lx) < static_cast<unsigned>(p.cw);
+                    const u32x4 u = *reinterpret_cast<const u32x4*>(&conv[(ly * TC + lx) * STEM_LD + chunk * 8]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        m[2 * e] = fmaxf(m[2 * e], in ? bf_lo(u[e]) : -INFINITY);
+                        m[2 * e + 1] = fmaxf(m[2 * e + 1], in ? bf_hi(u[e]) : -INFINITY);
+                    }
+                }
+            bf16x8 o;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = (__bf16)m[e];
+            *reinterpret_cast<bf16x8*>(p.y + ((static_cast<int64_t>(img) * p.ph + oy) * p.pw + ox) * p.ldc + n) = o;
+        }
+    } else {
+        for (int q = tid; q < NPIX * 8; q += 256) {
+            const int chunk = q & 7, pix = q >> 3, oy = 16 * ty + (pix >> 4), ox = 16 * tx + (pix & 15), n = n0 + chunk * 8;
+            if (oy >= p.ch || ox >= p.cw || n >= p.cout) continue;
+            *reinterpret_cast<u32x4*>(p.y + ((static_cast<int64_t>(img) * p.ch + oy) * p.cw + ox) * p.ldc + n) =
+                *reinterpret_cast<const u32x4*>(&conv[pix * STEM_LD + chunk * 8]);
+        }
+    }
+}
+
+}  // namespace
+
+// (GELU keeps the general path: its formula lives with the GEMM's epilogues)
+bool stem_ok(int dtype, int c, int kh, int kw, int stride, int cout, int64_t ldc, int64_t out_off, int act, bool res) {
+    return dtype == MOPAR_BF16 && c <= 4 && kh == STEM_K && kw == STEM_K && stride == 2 && cout % 8 == 0 && ldc % 8 == 0 &&
+           out_off % 8 == 0 && act != MOPAR_ACT_GELU && !res;
+}
+
+hipError_t launch_stem(const float* x, const void* w, const void* b, void* y, int n, int c, int h, int wd, int pad, int ch,
+                       int cw, int ph, int pw, int cout, int64_t ldc, int act, bool pool, hipStream_t s) {
+    StemParams p{};
+    p.x = x;
+    p.w = static_cast<const __bf16*>(w);
+    p.b = static_cast<const __bf16*>(b);
+    p.y = static_cast<__bf16*>(y);
+    p.c = c, p.h = h, p.wd = wd, p.pad = pad, p.ch = ch, p.cw = cw, p.ph = ph, p.pw = pw;
+    p.cout = cout, p.ldc = static_cast<int>(ldc), p.act = act;
+    const int oh = pool ? ph : ch, ow = pool ? pw : cw, edge = pool ? 8 : 16;
+    const int64_t tyn = (oh + edge - 1) / edge, txn = (ow + edge - 1) / edge, blocks = tyn * txn * n;
+    if (int64_t(c) * h * wd * 4 >= (int64_t(1) << 31) || c < 1 || c > 4) return hipErrorInvalidValue;
+    if (blocks >= (int64_t(1) << 31) || (cout + 63) / 64 > 65535) return hipErrorInvalidValue;
+    p.tiles = static_cast<int>(tyn * txn), p.tx = static_cast<int>(txn);
+    const dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>((cout + 63) / 64));
+    if (pool)
+        launch_kernel(stem_kernel<true>, grid, dim3(256), 0, s, p);
+    else
+        launch_kernel(stem_kernel<false>, grid, dim3(256), 0, s, p);
+    return hipGetLastError();
+}
+
 size_t dtype_size(int dtype) { return dtype == MOPAR_BF16 ? 2 : 4; }
 
 }  // namespace mopar

@@ -38,6 +38,8 @@ struct OpInfo {
     int partial_temp = -1;         // index into temps of the split-K partial sums
     int cs = 0;                    // conv: input channel storage stride (padded for the model input)
     bool input_is_model = false;   // conv: reads the NCHW float32 model input
+    bool stem = false;             // conv: runs on the first-layer kernel
+    bool pool_next = false;        // ... and the next op is the only reader of its result, a pool it can do in the same pass
     int64_t K = 0, M = 0;          // GEMM sizes (conv / linear)
     std::vector<size_t> temps;     // scratch buffers needed while this op runs
     std::vector<size_t> temp_off;  // their workspace offsets
@@ -329,6 +331,8 @@ static int validate_and_build(mopar_model_s& m) {
                 if (!xin && x.dims[1] % epc != 0)
                     return set_error(MOPAR_E_UNSUPPORTED, nm + ": input channels must be a multiple of " +
                                                               std::to_string(epc));
+                inf.stem = xin && stem_ok(m.dtype, static_cast<int>(x.dims[1]), op.kh, op.kw, op.stride, op.n_out, y.dims[1],
+                                          op.out_off, op.act, op.in1 >= 0);
                 inf.cs = static_cast<int>(xin ? round_up(x.dims[1], epc) : x.dims[1]);
                 inf.K = static_cast<int64_t>(op.kh) * op.kw * inf.cs;
                 inf.M = x.dims[0] * ho * wo;
@@ -473,6 +477,16 @@ static int validate_and_build(mopar_model_s& m) {
             if (m.cross[j].empty()) return set_error(MOPAR_E_ARG, "model: nothing crosses the cut after node " + std::to_string(j));
     }
 
+    for (int i = 0; i + 1 < static_cast<int>(m.ops.size()); ++i) {
+        const auto &op = m.ops[i], &nx = m.ops[i + 1];
+        if (!m.info[i].stem || op.n_out != m.tensors[op.out].dims[1] || nx.kind != MOPAR_OP_MAXPOOL || nx.in0 != op.out ||
+            nx.kh != 3 || nx.stride != 2 || nx.pad != 1)
+            continue;
+        int readers = 0;
+        for (const auto& o : m.ops) readers += (o.in0 == op.out) + (o.in1 == op.out);
+        m.info[i].pool_next = readers == 1;
+    }
+
     // workspace: every tensor except the model input and output gets a slot, live from
     // its producer to its last reader; op scratch lives for its op.  First-fit reuse.
     std::vector<int> last_use(nt, -1);
@@ -602,6 +616,13 @@ static hipError_t run_op(const mopar_model_s& m, int i, const Ptrs& P, int ksub,
     switch (op.kind) {
         case MOPAR_OP_CONV: {
             const void* src = P.get(op.in0);
+            if (inf.stem) {
+                void* dst = static_cast<unsigned char*>(P.get(op.out)) + static_cast<size_t>(op.out_off) * elt_bytes(dt);
+                return launch_stem(static_cast<const float*>(src), W(m, op.w), W(m, op.b), dst, static_cast<int>(x.dims[0]),
+                                   static_cast<int>(x.dims[1]), static_cast<int>(x.dims[2]), static_cast<int>(x.dims[3]),
+                                   op.pad, static_cast<int>(y.dims[2]), static_cast<int>(y.dims[3]), 0, 0, op.n_out,
+                                   y.dims[1], op.act, false, s);
+            }
             if (inf.input_is_model) {
                 void* tmp = P.ws + inf.temp_off[0];
                 hipError_t e = launch_nchw_to_nhwc(static_cast<const float*>(src), tmp, static_cast<int>(x.dims[0]),
@@ -736,6 +757,16 @@ static hipError_t run_op(const mopar_model_s& m, int i, const Ptrs& P, int ksub,
     }
 }
 
+// A first-layer conv and the max pool after it in one pass (OpInfo::pool_next)
+static hipError_t run_stem_pool(const mopar_model_s& m, int i, const Ptrs& P, hipStream_t s) {
+    const auto &op = m.ops[i], &pl = m.ops[i + 1];
+    const auto &x = m.tensors[op.in0], &y = m.tensors[op.out], &z = m.tensors[pl.out];
+    return launch_stem(static_cast<const float*>(P.get(op.in0)), W(m, op.w), W(m, op.b), P.get(pl.out),
+                       static_cast<int>(x.dims[0]), static_cast<int>(x.dims[1]), static_cast<int>(x.dims[2]),
+                       static_cast<int>(x.dims[3]), op.pad, static_cast<int>(y.dims[2]), static_cast<int>(y.dims[3]),
+                       static_cast<int>(z.dims[2]), static_cast<int>(z.dims[3]), op.n_out, y.dims[1], op.act, true, s);
+}
+
 // Runs `fn` (which enqueues work on s), bracketed by the events of `slot` when timing is on.
 template <typename F>
 static hipError_t timed(const mopar_model_s& mc, int slot, hipStream_t s, F&& fn) {
@@ -759,11 +790,17 @@ static void reset_timing(const mopar_model_s& mc) {
 }
 
 static int run_layers(const mopar_model_s& m, const mopar_plan& p, int l0, int l1, const Ptrs& P, hipStream_t s) {
+    int skip = -1;                                // an op done in the pass of the one before it
     for (int l = l0; l <= l1; ++l)
         for (int i = m.layer_first[l]; i <= m.layer_last[l]; ++i) {
+            if (i == skip) continue;
             const int ksub = m.ops[i].rd ? p.k[l] : 1;
-            const hipError_t e = timed(m, i, s, [&] { return run_op(m, i, P, ksub, s); });
+            // (per-op timing runs the ops one by one: the same bits)
+            const bool fuse = !m.timing && m.info[i].pool_next && i + 1 <= m.layer_last[l1];
+            const hipError_t e = fuse ? run_stem_pool(m, i, P, s)
+                                      : timed(m, i, s, [&] { return run_op(m, i, P, ksub, s); });
             if (e != hipSuccess) return hip_check(e, "kernel launch");
+            if (fuse) skip = i + 1;
         }
     return MOPAR_OK;
 }
