@@ -866,8 +866,8 @@ __global__ __launch_bounds__(WM * WN * KS * 64) void gemm_kernel(const GemmParam
 }
 
 // ---------------------------------------------------------------------------
-// Large bf16 products (see pp_class): 256 x 256 block tiles on v_mfma_f32_32x32x16_bf16, eight
-// waves in two groups that take turns on the matrix units.
+// Large bf16 products (see pp_tile): 256 x 256 or 128 x 128 block tiles on v_mfma_f32_32x32x16_bf16,
+// eight waves in two groups that take turns on the matrix units.
 //
 // Waves 0-3 (one per SIMD) own the upper 128 rows of the tile, waves 4-7 the lower ones, each a
 // 128 x 64 part (8 accumulator tiles, 128 registers).  A 64-wide k tile is worked in two phases,
@@ -883,6 +883,10 @@ __global__ __launch_bounds__(WM * WN * KS * 64) void gemm_kernel(const GemmParam
 // read in the first phase and reloaded for the k tile after next in the second; A1 is read in the
 // second and reloaded in the first of the next k tile: at the end of every memory step the loads
 // the next one needs are a k tile old (~2300 cycles) and the eight issued since stay in flight.
+//
+// Products with too few 256-wide tiles to fill the CUs take 128 x 128 ones: a wave owns 64 x 32, a k tile is
+// one phase of 8 MFMAs, a stage 32 KB, and four stages ring through the same 128 KB, the loads three k
+// tiles ahead (a k tile takes 0.4-0.5 us; gemm_kernel's 128 x 64 tiles 0.6-1 us).
 //
 // A block runs up to kPPChunk tiles; the load stream goes on into the next tile during the last k
 // tiles of the current one, so set-up and first-stage latency are paid once per block.  The 32
@@ -908,7 +912,6 @@ __global__ __launch_bounds__(WM * WN * KS * 64) void gemm_kernel(const GemmParam
 // ---------------------------------------------------------------------------
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-constexpr int kPPTile = 256;
 constexpr int kPPChunk = 4;        // most tiles of one block
 constexpr int kPPGroupM = 8;       // m tiles per group in the block order
 
@@ -929,11 +932,14 @@ __device__ __forceinline__ u32x4 load_any16(const void* q) {
 }
 __device__ __forceinline__ void store_any16(void* q, u32x4 v) { __builtin_memcpy(__builtin_assume_aligned(q, 2), &v, 16); }
 
-template <bool CONV, int EPI, int ACT>
+template <int TILE, bool CONV, int EPI, int ACT>
 __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
     using T = __bf16;
-    constexpr unsigned HALF = 16384, STAGE = 4 * HALF;   // bytes: A0 A1 B0 B1
-    __shared__ uint4 lds[2 * STAGE / 16];
+    constexpr int TM = TILE / 2, TN = TILE / 4;          // a wave's part of C
+    constexpr int IA = TM / 32, NJ = TN / 32;            // its 32 x 32 tiles
+    constexpr int HALVES = TILE / 128;                   // 128-row halves of an operand's stage
+    constexpr unsigned HALF = 16384, STAGE = 2 * HALVES * HALF, RING = 131072;   // bytes: a stage holds A0 (A1) B0 (B1)
+    __shared__ uint4 lds[RING / 16];
     touch_kernargs<sizeof(GemmParams)>();
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -956,8 +962,8 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
         const bool last = static_cast<int>(group) == (p.g_mt - 1) / kPPGroupM;
         const unsigned gm = last ? static_cast<unsigned>(p.g_mt - group * kPPGroupM) : kPPGroupM;
         const unsigned nti = last ? p.g_div_last.div(within) : within / kPPGroupM;
-        tl.n0 = __builtin_amdgcn_readfirstlane(static_cast<int>(nti) * kPPTile);
-        tl.m0 = __builtin_amdgcn_readfirstlane(static_cast<int>(group * kPPGroupM + (within - nti * gm)) * kPPTile);
+        tl.n0 = __builtin_amdgcn_readfirstlane(static_cast<int>(nti) * TILE);
+        tl.m0 = __builtin_amdgcn_readfirstlane(static_cast<int>(group * kPPGroupM + (within - nti * gm)) * TILE);
         return true;
     };
     Tile cur, ahead;
@@ -989,12 +995,12 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
     unsigned lds_dst = static_cast<unsigned>(wave) * 64u;   // where this wave's loads go, in uint4 (stage 0 or 1)
     auto offsets = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < HALVES; ++h)
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
                 const int r = (wave + 8 * s) * 8 + (lane >> 3);
-                const int m = min(ahead.m0 + (r >> 6) * 128 + h * 64 + (r & 63), Mi - 1);
-                const int n = min(ahead.n0 + (r >> 5) * 64 + h * 32 + (r & 31), p.N - 1);
+                const int m = min(ahead.m0 + (r >> 6) * TM + h * 64 + (r & 63), Mi - 1);
+                const int n = min(ahead.n0 + (r >> 5) * TN + h * 32 + (r & 31), p.N - 1);
                 if constexpr (CONV) {
                     const unsigned mu = static_cast<unsigned>(m);
                     const unsigned img = p.div_hw.div(mu);
@@ -1025,11 +1031,11 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
     auto load_b = [&](auto h) __attribute__((always_inline)) {
 #pragma unroll
         for (int s = 0; s < 2; ++s)
-            buffer_load_lds(p.B, p.b_bytes, (lds_ptr_t)(lds + lds_dst + (2 + h) * (HALF / 16) + s * 512), vb[2 * h + s], koff_b);
+            buffer_load_lds(p.B, p.b_bytes, (lds_ptr_t)(lds + lds_dst + (HALVES + h) * (HALF / 16) + s * 512), vb[2 * h + s], koff_b);
     };
     // the load stream to the next k tile: of the same tile, or the first of the block's next one
     auto stream_next = [&]() __attribute__((always_inline)) {
-        lds_dst ^= STAGE / 16;
+        lds_dst = (lds_dst + STAGE / 16) & (RING / 16 - 1);
         koff_b += 128;
         koff_a += 128;
         ++ikt;
@@ -1067,14 +1073,23 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
     using I1 = std::integral_constant<int, 1>;
 
     offsets();
-    load_b(I0{});                              // prologue: k tile 0, and k tile 1 but for A1 (nk >= 2)
-    load_b(I1{});
-    load_a(I0{});
-    load_a(I1{});
-    stream_next();
-    load_b(I0{});
-    load_b(I1{});
-    load_a(I0{});
+    if constexpr (TILE == 256) {               // prologue: k tile 0, and k tile 1 but for A1
+        load_b(I0{});
+        load_b(I1{});
+        load_a(I0{});
+        load_a(I1{});
+        stream_next();
+        load_b(I0{});
+        load_b(I1{});
+        load_a(I0{});
+    } else {                                   // k tiles 0, 1 and 2
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            if (u) stream_next();
+            load_b(I0{});
+            load_a(I0{});
+        }
+    }
 
     // --- fragments ------------------------------------------------------------------------------
     // lane's 16 bytes of k step kk (16 wide): row l % 32 of a 32-row tile, chunk 2 kk + l / 32
@@ -1086,21 +1101,26 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
         fa[kk] = f + wm * 8192;
         fb[kk] = f + wn * 4096;
     }
-    u32x4 af[2][4], bf[2][4];
-    f32x16 acc[2][2][2];                       // [A half][row tile][B half]
+    u32x4 af[2][4], bf[NJ][4];
+    f32x16 acc[HALVES][2][NJ];                 // [A half][row tile][B half]
+    unsigned roff = 0;                         // stage the fragments come from, in bytes
     bool stored = false;                       // the block has stored a tile, with a known number of stores per wave
     // An MFMA step, after the reads and loads of its memory step: wait for the reads and for the loads
     // that the next memory step reads, the eight issued since staying in flight (in a tile's first
-    // k tile the previous tile's 16 stores, 32 of float32 results, lie between them)
+    // k tile the previous tile's stores lie between them)
+    constexpr int STORES = IA * NJ * (EPI == PP_F32 ? 4 : 2);
     auto mfma_step = [&](auto i, auto first) __attribute__((always_inline)) {
         if (decltype(first)::value && stored)
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(EPI == PP_F32 ? 40 : 24) : "memory");
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(8 + STORES) : "memory");
         else
             asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
             pin(af[0][kk]), pin(af[1][kk]);
-            if constexpr (i == 0) pin(bf[0][kk]), pin(bf[1][kk]);
+            if constexpr (i == 0) {
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) pin(bf[j][kk]);
+            }
         }
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
@@ -1110,7 +1130,7 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
 #pragma unroll
             for (int a = 0; a < 2; ++a)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < NJ; ++j)
                     acc[i][a][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bf[j][kk]),
                                                                            __builtin_bit_cast(bf16x8, af[a][kk]), acc[i][a][j], 0, 0, 0);
         __builtin_amdgcn_s_setprio(0);
@@ -1119,62 +1139,68 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
     };
     auto read_a = [&](auto h) __attribute__((always_inline)) {
         static_for<4>([&](auto kk) __attribute__((always_inline)) {
-            af[0][kk] = lds_read16_at<h * HALF>(fa[kk]);
-            af[1][kk] = lds_read16_at<h * HALF + 4096>(fa[kk]);
+            af[0][kk] = lds_read16_at<h * HALF>(fa[kk] + roff);
+            af[1][kk] = lds_read16_at<h * HALF + 4096>(fa[kk] + roff);
         });
     };
     auto read_b = [&]() __attribute__((always_inline)) {
         static_for<4>([&](auto kk) __attribute__((always_inline)) {
-            bf[0][kk] = lds_read16_at<2 * HALF>(fb[kk]);
-            bf[1][kk] = lds_read16_at<3 * HALF>(fb[kk]);
+            static_for<NJ>([&](auto j) __attribute__((always_inline)) { bf[j][kk] = lds_read16_at<(HALVES + j) * HALF>(fb[kk] + roff); });
         });
     };
     auto ktile = [&](auto first) __attribute__((always_inline)) {
         read_b();
         read_a(I0{});
-        load_a(I1{});
-        stream_next();
-        mfma_step(I0{}, first);
-        read_a(I1{});
-        load_b(I0{});
-        load_b(I1{});
-        load_a(I0{});
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) fa[kk] ^= STAGE, fb[kk] ^= STAGE;
-        mfma_step(I1{}, first);
+        if constexpr (TILE == 256) {
+            load_a(I1{});
+            stream_next();
+            mfma_step(I0{}, first);
+            read_a(I1{});
+            load_b(I0{});
+            load_b(I1{});
+            load_a(I0{});
+            roff ^= STAGE;
+            mfma_step(I1{}, first);
+        } else {
+            stream_next();
+            load_b(I0{});
+            load_a(I0{});
+            roff = (roff + STAGE) & (RING - 1);
+            mfma_step(I0{}, first);
+        }
     };
 
-    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");    // B and A0 of k tile 0
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");    // what the first phase of k tile 0 reads
     __builtin_amdgcn_s_barrier();
     if (wave >= 4) __builtin_amdgcn_s_barrier();        // the second group runs one step behind
     for (;;) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < HALVES; ++i)
 #pragma unroll
             for (int a = 0; a < 2; ++a)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < NJ; ++j)
 #pragma unroll
                     for (int e = 0; e < 16; ++e) acc[i][a][j][e] = 0.0f;
         ktile(std::true_type{});
         for (int kt = 1; kt < nk; ++kt) ktile(std::false_type{});
-        // --- epilogue: rows m0 + 128 wm + 64 i + 32 a + l % 32, columns n0 + 64 wn + 32 j + 8 g + 4 (l / 32) ..
-        const int nb = cur.n0 + wn * 64;
+        // --- epilogue: rows m0 + TM wm + 32 ia + l % 32, columns n0 + TN wn + 32 j + 8 g + 4 (l / 32) .. + 3
+        const int nb = cur.n0 + wn * TN;
         if constexpr (EPI != PP_ANY) {
             // results and residual go through buffer resources: a row or group that is not stored gets an
             // offset past the end, so every lane issues the same stores
             const auto crs = buffer_rsrc(p.C, static_cast<int>(p.c_bytes));
             const auto rrs = buffer_rsrc(p.res, p.res ? static_cast<int>(p.c_bytes) : 0);
-            // the wave's 64 columns of bias, through the scalar cache: a vector load would be waited for
+            // the wave's columns of bias, through the scalar cache: a vector load would be waited for
             // behind the operand loads in flight (groups past the end re-read the last one)
-            u32x2 rb[2][4], rb2[2][4];
+            u32x2 rb[NJ][4], rb2[NJ][4];
             auto group_bias = [&](const void* base, int n) __attribute__((always_inline)) -> u32x2 {
                 const auto* src = (const __attribute__((address_space(4))) unsigned char*)(base ? base : kZeroChunk);
                 const u32x4 q = *(const __attribute__((address_space(4))) u32x4*)(src + (base ? min(n, p.N - 8) * 2 : 0));
                 return u32x2{lhalf ? q[2] : q[0], lhalf ? q[3] : q[1]};
             };
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < NJ; ++j)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     rb[j][g] = group_bias(p.bias, nb + j * 32 + g * 8);
@@ -1184,33 +1210,33 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
             // than 2^31 bytes: 0x7fffffff plus any row, and 2^31 plus any column, lie past it)
             constexpr unsigned ESZ = EPI == PP_F32 ? 4u : 2u;
             auto row_off = [&](int ia) __attribute__((always_inline)) -> unsigned {
-                const int m = cur.m0 + wm * 128 + ia * 32 + lrow;
+                const int m = cur.m0 + wm * TM + ia * 32 + lrow;
                 return m < Mi ? static_cast<unsigned>(m) * static_cast<unsigned>(p.ldc * ESZ) : kOOB;
             };
             // bf16: the group of eight columns a lane moves, 2 gp (lanes 0-31) or 2 gp + 1 (32-63); float32: the
             // lane's four columns of group g
-            unsigned col_off[2][EPI == PP_F32 ? 4 : 2];
+            unsigned col_off[NJ][EPI == PP_F32 ? 4 : 2];
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < NJ; ++j)
 #pragma unroll
                 for (int g = 0; g < (EPI == PP_F32 ? 4 : 2); ++g) {
                     const int n = nb + j * 32 + (EPI == PP_F32 ? g * 8 + lhalf * 4 : (2 * g + lhalf) * 8);
                     col_off[j][g] = n < p.N ? static_cast<unsigned>(n) * ESZ : 0x7fffffffu;
                 }
-            u32x4 rr[2][2];
+            u32x4 rr[NJ][2];
             auto load_res = [&](unsigned row) __attribute__((always_inline)) {
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < NJ; ++j)
 #pragma unroll
                     for (int gp = 0; gp < 2; ++gp)
                         rr[j][gp] = __builtin_amdgcn_raw_buffer_load_b128(rrs, static_cast<int>(row + col_off[j][gp]), 0, 0);
             };
             auto store_bf16 = [&]() __attribute__((always_inline)) {
-                static_for<4>([&](auto ia) __attribute__((always_inline)) {
+                static_for<IA>([&](auto ia) __attribute__((always_inline)) {
                     const unsigned row = row_off(ia);
                     if constexpr (EPI == PP_RES) load_res(row);
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
+                    for (int j = 0; j < NJ; ++j)
 #pragma unroll
                         for (int gp = 0; gp < 2; ++gp) {
                             float rs[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
@@ -1245,10 +1271,10 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
                 });
             };
             if constexpr (EPI == PP_F32) {
-                static_for<4>([&](auto ia) __attribute__((always_inline)) {
+                static_for<IA>([&](auto ia) __attribute__((always_inline)) {
                     const unsigned row = row_off(ia);
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
+                    for (int j = 0; j < NJ; ++j)
 #pragma unroll
                         for (int g = 0; g < 4; ++g) {
                             u32x4 v;
@@ -1268,11 +1294,11 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
             const T* const biasp = static_cast<const T*>(p.bias);
             const T* const resp = static_cast<const T*>(p.res);
             T* const C = static_cast<T*>(p.C);
-            const bool tail = cur.n0 + kPPTile > p.N;
-            u32x2 rb[2][4];
+            const bool tail = cur.n0 + TILE > p.N;
+            u32x2 rb[NJ][4];
             const auto brs = buffer_rsrc(biasp, biasp ? p.N * 2 : 0);
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < NJ; ++j)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const int o = (nb + j * 32 + g * 8 + lhalf * 4) * 2;
@@ -1286,11 +1312,11 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
                         if (biasp) rb[j][g] = *(const __attribute__((address_space(1))) u32x2*)(reinterpret_cast<const char*>(biasp) + o);
                     }
                 }
-            static_for<4>([&](auto ia) __attribute__((always_inline)) {
-                const int m = cur.m0 + wm * 128 + ia * 32 + lrow;
+            static_for<IA>([&](auto ia) __attribute__((always_inline)) {
+                const int m = cur.m0 + wm * TM + ia * 32 + lrow;
                 const int64_t row = static_cast<int64_t>(min(m, Mi - 1)) * p.ldc;
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < NJ; ++j)
 #pragma unroll
                     for (int gp = 0; gp < 2; ++gp) {
                         const int n = nb + j * 32 + (2 * gp + lhalf) * 8;
@@ -1334,7 +1360,7 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
             });
         }
         stored = EPI != PP_ANY;   // (there the number of stores issued depends on the lanes: counted as none)
-        // the load stream has at least begun the next tile (it runs two k tiles ahead)
+        // the load stream has at least begun the next tile (it runs two k tiles ahead, or three)
         if (!live) break;
         cur = ahead;
     }
@@ -1674,35 +1700,42 @@ static hipError_t launch_cfg(const GemmParams& params, int width, hipStream_t st
     return hipGetLastError();
 }
 
-// Whether an operator runs on gemm_pp_kernel: a function of its (M, N, K), geometry and alignment-free
-// properties alone, never of the sub-slice count, so that all its sub-slice launches run the same
-// arithmetic (a tile may hold columns of several sub-slices).  A block fills a CU, so the line lies at
-// the share of the CUs that the last round of tiles leaves idle.  Measured against gemm_kernel's tiles
-// (us, this kernel / gemm_kernel): 4096 x 768 -> 2304, 144 tiles, 23.6 / 30.9; -> 3072, 192 tiles, 25.0 /
-// 30.3; 3x3 convs over 56 x 56 x 256, 147 tiles, 56 / 68.5; 98 tiles, 52.5 / 43.9; 8192 x 1024 -> 1024, 128
-// tiles, 26.6 / 24.1; and in two rounds 600 x 1024 -> 25047, 294 tiles, 63.4 / 55.9; 8192 x 768 -> 3072, 384
-// tiles, 45.6 / 54.5; 8229 x 312 -> 8000, 1056 tiles, 73 / 94.
-static bool pp_class(const GemmParams& p) {
+// The tile of an operator that runs on gemm_pp_kernel (0: it does not): a function of its (M, N, K) and
+// geometry alone, never of the sub-slice count, so that all its sub-slice launches run the same arithmetic
+// (a tile may hold columns of several sub-slices).  A block fills a CU, so the lines lie at the share of the
+// CUs that the last round of tiles leaves idle.  Measured against gemm_kernel's tiles (us, here / there).
+// 256: 4096 x 768 -> 2304, 144 tiles, 23.6 / 30.9; -> 3072, 192 tiles, 25.0 / 30.3; 3x3 convs over 56 x 56 x 256,
+// 147 tiles, 56 / 68.5, 98 tiles, 52.5 / 43.9; 8192 x 1024 -> 1024, 128 tiles, 26.6 / 24.1; in two rounds 600 x
+// 1024 -> 25047, 294 tiles, 63.4 / 55.9, 8192 x 768 -> 3072, 384 tiles, 45.6 / 54.5; 8229 x 312 -> 8000, 1056
+// tiles, 73 / 94.  128, one round: the conv over 56 x 56 x 256, 196 tiles, 28.9 / 34.9, over 28 x 28 x 512, 196
+// tiles, 45.8 / 56.6, over 112 x 112 x 128, 196 tiles, 20.3 / 23.5; 2048 x 1024 -> 1024, 128 tiles, 12.3 / 11.7; in two
+// rounds only short K: 8192 x 256 -> 1024 12.3 / 14.2, 8192 x 512 -> 1024 16.2 / 17.3, 8192 x 1024 -> 1024 25.0 /
+// 24.1, the conv over 56 x 56 x 256, 392 tiles, 50 / 44.
+static int pp_tile(const GemmParams& p) {
     // (the output span is addressed with 32-bit offsets, below the out-of-range offset 2^31)
     const int64_t c_span = ((p.M - 1) * p.ldc + p.N) * (p.out_f32 ? 4 : 2);
-    if (p.thin || p.epi != EPI_STD || p.splits != 1 || c_span >= (int64_t(1) << 31)) return false;
+    if (p.thin || p.epi != EPI_STD || p.splits != 1 || c_span >= (int64_t(1) << 31)) return 0;
     // float32 results and second biases: the LSTM's input projection only
-    if (p.out_f32 && (p.conv || p.res || p.act != MOPAR_ACT_NONE || p.N % 8 != 0 || p.ldc % 8 != 0)) return false;
-    if (p.bias2 && !p.out_f32) return false;
+    if (p.out_f32 && (p.conv || p.res || p.act != MOPAR_ACT_NONE || p.N % 8 != 0 || p.ldc % 8 != 0)) return 0;
+    if (p.bias2 && !p.out_f32) return 0;
     // a 64-wide k tile of a conv lies in one tap, and a tap has a bit of a 32-bit mask; the operand and
     // the rows of padding before it are addressed together
     if (p.conv && (p.cs % 64 != 0 || p.kh * p.kw > 32 || p.pad >= p.img_w ||
                    int64_t(p.a_bytes) + (int64_t(p.pad) * p.img_w + p.pad) * p.cs * 2 >= (int64_t(1) << 31)))
-        return false;
-    const int64_t tiles = ((p.M + kPPTile - 1) / kPPTile) * ((p.N + kPPTile - 1) / kPPTile);
-    const int64_t rounds = (tiles + kCUs - 1) / kCUs;
-    return p.K >= 256 && p.N >= 192 && (rounds == 1 ? tiles >= 140 : tiles * 10 >= rounds * kCUs * 6);
+        return 0;
+    if (p.K < 256) return 0;
+    const int64_t tiles = ((p.M + 255) / 256) * ((p.N + 255) / 256), rounds = (tiles + kCUs - 1) / kCUs;
+    if (p.N >= 192 && (rounds == 1 ? tiles >= 140 : tiles * 10 >= rounds * kCUs * 6)) return 256;
+    const int64_t small = ((p.M + 127) / 128) * ((p.N + 127) / 128), srounds = (small + kCUs - 1) / kCUs;
+    if (p.N >= 96 && (srounds == 1 ? small >= 140 : p.K <= 512 && small * 4 >= srounds * kCUs * 3)) return 128;
+    return 0;
 }
 
+template <int TILE>
 static hipError_t launch_pp(const GemmParams& params, hipStream_t st) {
     GemmParams p = params;
     p.c_bytes = static_cast<uint32_t>(((p.M - 1) * p.ldc + p.N) * (p.out_f32 ? 4 : 2));
-    const int64_t mt = (p.M + kPPTile - 1) / kPPTile, nt = (p.N + kPPTile - 1) / kPPTile;
+    const int64_t mt = (p.M + TILE - 1) / TILE, nt = (p.N + TILE - 1) / TILE;
     const int64_t total = mt * nt;
     if (total >= (int64_t(1) << 31) / kPPGroupM) return hipErrorInvalidValue;
     p.g_mt = static_cast<int>(mt);
@@ -1713,7 +1746,7 @@ static hipError_t launch_pp(const GemmParams& params, hipStream_t st) {
     p.g_div_group = FastDiv(static_cast<unsigned>(kPPGroupM * p.g_nt));
     const int last = static_cast<int>(mt - (mt - 1) / kPPGroupM * kPPGroupM);
     p.g_div_last = FastDiv(static_cast<unsigned>(last));
-    if (p.g_nk < 2) return hipErrorInvalidValue;
+    if (p.g_nk < (TILE == 256 ? 2 : 3)) return hipErrorInvalidValue;
     // tiles per block: one round of 32 blocks per XCD where that is at most kPPChunk tiles each
     const int rounds = (p.g_per_xcd + 31) / 32;
     p.g_chunk = rounds < kPPChunk ? rounds : kPPChunk;
@@ -1723,24 +1756,24 @@ static hipError_t launch_pp(const GemmParams& params, hipStream_t st) {
     const bool regular = p.N % 8 == 0 && p.ldc % 8 == 0 &&
                          ((reinterpret_cast<uintptr_t>(p.C) | reinterpret_cast<uintptr_t>(p.res) |
                            reinterpret_cast<uintptr_t>(p.bias) | reinterpret_cast<uintptr_t>(p.bias2)) & 15) == 0;
-    if (p.out_f32 && (!regular || p.conv)) return hipErrorInvalidValue;   // not in pp_class
+    if (p.out_f32 && (!regular || p.conv)) return hipErrorInvalidValue;   // see pp_tile
     const dim3 g(grid), b(512);
     auto go_act = [&](auto conv, auto epi) {
         constexpr bool C = decltype(conv)::value;
         constexpr int E = decltype(epi)::value;
         if (p.act == MOPAR_ACT_RELU)
-            launch_kernel(gemm_pp_kernel<C, E, MOPAR_ACT_RELU>, g, b, 0, st, p);
+            launch_kernel(gemm_pp_kernel<TILE, C, E, MOPAR_ACT_RELU>, g, b, 0, st, p);
         else if (p.act == MOPAR_ACT_GELU)
-            launch_kernel(gemm_pp_kernel<C, E, MOPAR_ACT_GELU>, g, b, 0, st, p);
+            launch_kernel(gemm_pp_kernel<TILE, C, E, MOPAR_ACT_GELU>, g, b, 0, st, p);
         else
-            launch_kernel(gemm_pp_kernel<C, E, MOPAR_ACT_NONE>, g, b, 0, st, p);
+            launch_kernel(gemm_pp_kernel<TILE, C, E, MOPAR_ACT_NONE>, g, b, 0, st, p);
     };
     auto go = [&](auto conv) {
         constexpr bool C = decltype(conv)::value;
         if (!regular)
             go_act(conv, std::integral_constant<int, PP_ANY>{});
         else if (p.out_f32)
-            launch_kernel(gemm_pp_kernel<false, PP_F32, MOPAR_ACT_NONE>, g, b, 0, st, p);
+            launch_kernel(gemm_pp_kernel<TILE, false, PP_F32, MOPAR_ACT_NONE>, g, b, 0, st, p);
         else if (p.res)
             go_act(conv, std::integral_constant<int, PP_RES>{});
         else
@@ -1757,7 +1790,8 @@ template <typename T>
 static hipError_t dispatch(const GemmParams& p, hipStream_t st) {
     const int width = (p.N + p.ksub - 1) / p.ksub;   // widest sub-slice
     if constexpr (sizeof(T) == 2) {
-        if (pp_class(p)) return launch_pp(p, st);
+        const int tile = pp_tile(p);
+        if (tile) return tile == 256 ? launch_pp<256>(p, st) : launch_pp<128>(p, st);
     }
     // float32 products of at most 16 64 x 64 tiles (a batch-1 CNN's later convs and its classifier): the MFMA time
     // of a block and its serial K loop both count, so small tiles and K split over the waves
@@ -1789,6 +1823,10 @@ static hipError_t dispatch(const GemmParams& p, hipStream_t st) {
     const bool w128 = width >= 128 && (width + 127) / 128 * 128 * 10 <= width * 11;
     if (w128 && blocks(mt, 128) >= kCUs) return launch_cfg<T, 128, 128, 2, 4, 2>(p, width, st);
     if (width >= 64 && blocks(mt, 64) >= kCUs) return launch_cfg<T, 128, 64, 4, 2, 3>(p, width, st);
+    // under 200 blocks of 64 x 64: 32 x 32 tiles, four times as many (ResNet-50 on 2 images of 150 x 150 356 -> 328 us,
+    // its 1x1 convs of stage 3 at batch 8, 100 blocks, 8.2 -> 6.9 us)
+    if (sizeof(T) == 2 && width >= 64 && !p.thin && blocks((p.M + 63) / 64, 64) < 200)
+        return launch_cfg<T, 32, 32, 2, 2, 4>(p, width, st);
     if (width >= 64) return launch_cfg<T, 64, 64, 2, 4, 4>(p, width, st);
     if (width >= 32) {
         if (blocks(mt, 32) >= kCUs) return launch_cfg<T, 128, 32, 4, 2, 3>(p, width, st);

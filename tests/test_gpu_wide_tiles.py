@@ -17,6 +17,9 @@ pytestmark = pytest.mark.gpu
     (8961, 320, 1001, "relu", True, 4),      # rows at odd addresses, a last group of one column, residual
     (8960, 256, 1022, "none", False, 2),     # a last group of six columns
     (20001, 256, 1000, "none", True, 8),     # 79 x 4 tiles: two per block, residual
+    (4481, 264, 500, "gelu", False, 3),      # 128-wide tiles, 36 x 4: one row, 116 columns, 8 of k in the last ones
+    (4480, 576, 513, "relu", True, 4),       # 35 x 5, the last with one column; rows at odd addresses, residual
+    (12801, 256, 512, "none", True, 8),      # 101 x 4 in two rounds, residual
     (20001, 296, 1004, "gelu", True, 1),     # the same off the group, a last group of four columns
 ])
 def test_linear_edges(m, k, n, act, res, ksub):
@@ -36,6 +39,9 @@ def test_linear_edges(m, k, n, act, res, ksub):
     (10, 128, 61, 201, 3, 1, 1, True),       # odd width with a residual
     (9, 64, 126, 192, 3, 2, 1, False),       # strided
     (9, 64, 63, 192, 5, 1, 2, False),        # 25 taps, two pixels of padding
+    (5, 128, 61, 128, 3, 1, 1, True),        # 128-wide tiles: 146, residual
+    (5, 64, 123, 100, 3, 2, 1, False),       # 149, strided, 100 of 128 columns
+    (19, 256, 31, 132, 1, 2, 0, False),      # a strided 1x1 conv, 38 x 2 tiles stay on the general path
 ])
 def test_conv_edges(n, c, hw, cout, k, stride, pad, residual):
     mod = conv_model("bf16", n, c, hw, cout, k, stride, pad, residual=residual, pre=True)
