@@ -891,8 +891,10 @@ __global__ __launch_bounds__(WM * WN * KS * 64) void gemm_kernel(const GemmParam
 // A block runs up to kPPChunk tiles; the load stream goes on into the next tile during the last k
 // tiles of the current one, so set-up and first-stage latency are paid once per block.  The 32
 // blocks an XCD runs at a time work on 32 consecutive tiles of its run, in groups of 8 m tiles
-// that share operand rows in its L2.  The results are stored from the accumulators: a lane holds
-// four consecutive columns, and a half-wave swap makes them eight (one 16-byte store).
+// that share operand rows in its L2.  The results turn through 4 KB of LDS per wave so that a store
+// covers whole rows of the wave's part (128 bytes of bf16 or float32 a row; straight from the accumulators
+// a row got 32 bytes a store: 8192 x 1024 -> 32000 492 -> 473 us, 8000 x 1024 -> 31001 571 -> 530, and the LSTM
+// layer whose recurrence reads the float32 results next 515 -> 475).
 //
 // Arithmetic: acc = sum over k in 16-wide steps in ascending order from zero, then + (bias +
 // bias2), + residual, activation: a function of the op alone, so tiles run across the edges of
@@ -939,7 +941,8 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
     constexpr int IA = TM / 32, NJ = TN / 32;            // its 32 x 32 tiles
     constexpr int HALVES = TILE / 128;                   // 128-row halves of an operand's stage
     constexpr unsigned HALF = 16384, STAGE = 2 * HALVES * HALF, RING = 131072;   // bytes: a stage holds A0 (A1) B0 (B1)
-    __shared__ uint4 lds[RING / 16];
+    constexpr unsigned STG = 4096;                       // bytes per wave to turn 32 rows of results in
+    __shared__ uint4 lds[(RING + 8 * STG) / 16];
     touch_kernargs<sizeof(GemmParams)>();
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1186,6 +1189,27 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
         for (int kt = 1; kt < nk; ++kt) ktile(std::false_type{});
         // --- epilogue: rows m0 + TM wm + 32 ia + l % 32, columns n0 + TN wn + 32 j + 8 g + 4 (l / 32) .. + 3
         const int nb = cur.n0 + wn * TN;
+        // Results turn through LDS, 32 rows at a time in this wave's own space, so that a store covers whole
+        // rows of the wave's part: CPR 16-byte chunks a row, chunk c of row r at place c ^ (r % CPR).
+        constexpr int CPR = EPI == PP_F32 ? 8 : TN * 2 / 16, SROWS = 64 / CPR;   // (float32: one column tile at a time)
+        const unsigned stg = lds0 + RING + static_cast<unsigned>(wave) * STG;
+        auto put = [&](int chunk, int half8, auto v) __attribute__((always_inline)) {   // lane's 8 (16) bytes of its row
+            const unsigned a = stg + static_cast<unsigned>(lrow * CPR + (chunk ^ (lrow & (CPR - 1)))) * 16u + static_cast<unsigned>(half8 * 8);
+            if constexpr (sizeof(v) == 8)
+                asm volatile("ds_write_b64 %0, %1" ::"v"(a), "v"(v) : "memory");
+            else
+                asm volatile("ds_write_b128 %0, %1" ::"v"(a), "v"(v) : "memory");
+        };
+        const int sc = lane & (CPR - 1), sr = lane / CPR;
+        auto get = [&](u32x4 (&w)[32 / SROWS]) __attribute__((always_inline)) {   // chunk sc of rows sr, sr + SROWS, ...
+            static_for<32 / SROWS>([&](auto i) __attribute__((always_inline)) {
+                const int r = sr + i * SROWS;
+                w[i] = lds_read16(stg + static_cast<unsigned>(r * CPR + (sc ^ (r & (CPR - 1)))) * 16u);
+            });
+            lds_wait();
+#pragma unroll
+            for (int i = 0; i < 32 / SROWS; ++i) pin(w[i]);
+        };
         if constexpr (EPI != PP_ANY) {
             // results and residual go through buffer resources: a row or group that is not stored gets an
             // offset past the end, so every lane issues the same stores
@@ -1209,20 +1233,31 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
             // byte offsets: row + column, either past the result when it is not stored (results span less
             // than 2^31 bytes: 0x7fffffff plus any row, and 2^31 plus any column, lie past it)
             constexpr unsigned ESZ = EPI == PP_F32 ? 4u : 2u;
-            auto row_off = [&](int ia) __attribute__((always_inline)) -> unsigned {
-                const int m = cur.m0 + wm * TM + ia * 32 + lrow;
+            auto row_off = [&](int ia, int r) __attribute__((always_inline)) -> unsigned {
+                const int m = cur.m0 + wm * TM + ia * 32 + r;
                 return m < Mi ? static_cast<unsigned>(m) * static_cast<unsigned>(p.ldc * ESZ) : kOOB;
             };
-            // bf16: the group of eight columns a lane moves, 2 gp (lanes 0-31) or 2 gp + 1 (32-63); float32: the
-            // lane's four columns of group g
-            unsigned col_off[NJ][EPI == PP_F32 ? 4 : 2];
+            // residual: the group of eight columns a lane loads, 2 gp (lanes 0-31) or 2 gp + 1 (32-63)
+            unsigned col_off[NJ][2];
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
 #pragma unroll
-                for (int g = 0; g < (EPI == PP_F32 ? 4 : 2); ++g) {
-                    const int n = nb + j * 32 + (EPI == PP_F32 ? g * 8 + lhalf * 4 : (2 * g + lhalf) * 8);
+                for (int g = 0; g < 2; ++g) {
+                    const int n = nb + j * 32 + (2 * g + lhalf) * 8;
                     col_off[j][g] = n < p.N ? static_cast<unsigned>(n) * ESZ : 0x7fffffffu;
                 }
+            // the staged 32 rows to C: chunk sc (16 bytes from column byte col) of rows sr, sr + SROWS, ...
+            auto flush_rows = [&](int ia, unsigned col) __attribute__((always_inline)) {
+                u32x4 w[32 / SROWS];
+                get(w);
+#pragma unroll
+                for (int i = 0; i < 32 / SROWS; ++i) {
+                    __builtin_amdgcn_raw_buffer_store_b128(w[i], crs, static_cast<int>(row_off(ia, sr + i * SROWS) + col), 0, 0);
+                }
+            };
+            auto chunk_off = [&](int n) __attribute__((always_inline)) -> unsigned {
+                return n < p.N ? static_cast<unsigned>(n) * ESZ : 0x7fffffffu;
+            };
             u32x4 rr[NJ][2];
             auto load_res = [&](unsigned row) __attribute__((always_inline)) {
 #pragma unroll
@@ -1233,8 +1268,7 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
             };
             auto store_bf16 = [&]() __attribute__((always_inline)) {
                 static_for<IA>([&](auto ia) __attribute__((always_inline)) {
-                    const unsigned row = row_off(ia);
-                    if constexpr (EPI == PP_RES) load_res(row);
+                    if constexpr (EPI == PP_RES) load_res(row_off(ia, lrow));
 #pragma unroll
                     for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -1262,27 +1296,29 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
                                 }
                                 pk[h] = __builtin_bit_cast(u32x2, bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]});
                             }
-                            const u32x2 s0 = __builtin_amdgcn_permlane32_swap(pk[0][0], pk[1][0], false, false);
-                            const u32x2 s1 = __builtin_amdgcn_permlane32_swap(pk[0][1], pk[1][1], false, false);
-                            __builtin_amdgcn_raw_buffer_store_b128(u32x4{s0[0], s1[0], s0[1], s1[1]}, crs,
-                                                                   static_cast<int>(row + col_off[j][gp]), 0, 0);
+                            put(4 * j + 2 * gp, lhalf, pk[0]);
+                            put(4 * j + 2 * gp + 1, lhalf, pk[1]);
                         }
+                    lds_wait();
+                    flush_rows(ia, chunk_off(nb + sc * 8));
                     __builtin_amdgcn_sched_barrier(0);
                 });
             };
             if constexpr (EPI == PP_F32) {
                 static_for<IA>([&](auto ia) __attribute__((always_inline)) {
-                    const unsigned row = row_off(ia);
 #pragma unroll
-                    for (int j = 0; j < NJ; ++j)
+                    for (int j = 0; j < NJ; ++j) {
 #pragma unroll
                         for (int g = 0; g < 4; ++g) {
                             u32x4 v;
 #pragma unroll
                             for (int e = 0; e < 4; ++e) v[e] = __float_as_uint(acc[ia / 2][ia % 2][j][4 * g + e] +
                                                        (bf16_of(rb[j][g][e / 2], e & 1) + bf16_of(rb2[j][g][e / 2], e & 1)));
-                            __builtin_amdgcn_raw_buffer_store_b128(v, crs, static_cast<int>(row + col_off[j][g]), 0, 0);
+                            put(2 * g + lhalf, 0, v);
                         }
+                        lds_wait();
+                        flush_rows(ia, chunk_off(nb + j * 32 + sc * 4));
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                 });
             } else {
@@ -1345,17 +1381,25 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const GemmParams p) {
                                                  bf16_of(e < 2 ? r0[h] : r1[h], e & 1), ACT);
                             pk[h] = __builtin_bit_cast(u32x2, bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]});
                         }
-                        const u32x2 s0 = __builtin_amdgcn_permlane32_swap(pk[0][0], pk[1][0], false, false);
-                        const u32x2 s1 = __builtin_amdgcn_permlane32_swap(pk[0][1], pk[1][1], false, false);
-                        const u32x4 w = {s0[0], s1[0], s0[1], s1[1]};
-                        if (nv >= 8) {
-                            store_any16(C + row + n, w);
-                        } else if (nv > 0) {
-#pragma unroll
-                            for (int e = 0; e < 7; ++e)
-                                if (e < nv) reinterpret_cast<unsigned short*>(C + row + n)[e] = static_cast<unsigned short>(w[e / 2] >> (16 * (e & 1)));
-                        }
+                        put(4 * j + 2 * gp, lhalf, pk[0]);
+                        put(4 * j + 2 * gp + 1, lhalf, pk[1]);
                     }
+                lds_wait();
+                u32x4 w[32 / SROWS];
+                get(w);
+#pragma unroll
+                for (int i = 0; i < 32 / SROWS; ++i) {
+                    const int ms = cur.m0 + wm * TM + ia * 32 + sr + i * SROWS, n = nb + sc * 8;
+                    const int nv = ms < Mi ? p.N - n : 0;              // 8 or more: a whole group
+                    T* const dst = C + static_cast<int64_t>(min(ms, Mi - 1)) * p.ldc + n;
+                    if (nv >= 8) {
+                        store_any16(dst, w[i]);
+                    } else if (nv > 0) {
+#pragma unroll
+                        for (int e = 0; e < 7; ++e)
+                            if (e < nv) reinterpret_cast<unsigned short*>(dst)[e] = static_cast<unsigned short>(w[i][e / 2] >> (16 * (e & 1)));
+                    }
+                }
                 __builtin_amdgcn_sched_barrier(0);
             });
         }
