@@ -863,7 +863,7 @@ hipError_t launch_codec_narrow(const void* x, const void* w, const void* b, void
 // there, so the results equal the conv followed by the pool bit for bit.  The conv pixels on tile
 // borders are computed twice (289 for 256).
 //
-// ResNet-50's stem at batch 32 (224 x 224): 75 us as three kernels, 36 us here; at batch 8 33.6 -> 11.5 us.
+// ResNet-50's stem at batch 32 (224 x 224): 75 us as three kernels, 34.8 us here; at batch 8 33.6 -> 11.5 us.
 // It is bound by the latency of a block's phases (patch, weights, MFMAs, pool) with three blocks per
 // CU: 1568 blocks in two rounds.  Loads under branches cost most of it before they went through buffer
 // resources (52 us), weights read in fragment order 3 us more.
@@ -994,10 +994,14 @@ __global__ __launch_bounds__(256) void stem_kernel(const StemParams p) {
 #pragma unroll
         for (int r = 0; r < STEM_K; ++r) af[r] = *reinterpret_cast<const u32x4*>(src + r * PW);
     };
+    // the eighth column is no tap: its pixel counts as zero, or an infinity or NaN there would reach the sum
+    const unsigned tap8 = (lane >> 4) == 3 ? 0u : ~0u;
     auto compute = [&](int mt, u32x4 (&af)[STEM_K]) {
         f32x4 acc[2];
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[j] = f32x4{bias[j][0], bias[j][1], bias[j][2], bias[j][3]};
+#pragma unroll
+        for (int r = 0; r < STEM_K; ++r) af[r][2] &= tap8, af[r][3] &= tap8;
 #pragma unroll
         for (int r = 0; r < STEM_K; ++r)
 #pragma unroll

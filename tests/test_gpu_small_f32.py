@@ -54,6 +54,19 @@ def test_first_layer_conv_and_pool(n, c, hw, cout, pad, act):
     assert rel_err(_np(yc), oracle.forward(mc, x)) <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_first_layer_conv_keeps_a_non_finite_pixel_to_its_windows(bad):
+    x = synth.random_tensor((1, 3, 40, 40), "f32", seed=23)
+    x[0, 1, 17, 20] = bad                # one column right of the 7 taps of output column 8
+    m = stem_model(1, 3, (40, 40), 16, 3, "none", False)
+    y, _, _ = run_gpu(m, x, P.make_plan(1, [0], [1]))
+    got, ref = _np(y), oracle.forward(m, x)
+    assert 0 < (~np.isfinite(ref)).sum() < ref.size // 8
+    assert np.array_equal(np.isfinite(got), np.isfinite(ref))
+    ok = np.isfinite(ref)
+    assert rel_err(got[ok], ref[ok]) <= TOL["bf16"]
+
+
 def test_pool_of_a_tensor_read_twice_stays_its_own_pass():
     n, hw = 1, (40, 40)
     b = synth._Builder("stem2", "bf16", n, 18)
