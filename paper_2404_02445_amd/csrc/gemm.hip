@@ -1744,17 +1744,42 @@ static hipError_t launch_cfg(const GemmParams& params, int width, hipStream_t st
     return hipGetLastError();
 }
 
-// The tile of an operator that runs on gemm_pp_kernel (0: it does not): a function of its (M, N, K) and
-// geometry alone, never of the sub-slice count, so that all its sub-slice launches run the same arithmetic
+// The tile of gemm_pp_kernel for an (M, N, K) product (0: gemm_kernel's tiles are faster): a function of the
+// product alone, never of the sub-slice count, so that all sub-slice launches of an operator run the same arithmetic
 // (a tile may hold columns of several sub-slices).  A block fills a CU, so the lines lie at the share of the
 // CUs that the last round of tiles leaves idle.  Measured against gemm_kernel's tiles (us, here / there).
 // 256: 4096 x 768 -> 2304, 144 tiles, 23.6 / 30.9; -> 3072, 192 tiles, 25.0 / 30.3; 3x3 convs over 56 x 56 x 256,
 // 147 tiles, 56 / 68.5, 98 tiles, 52.5 / 43.9; 8192 x 1024 -> 1024, 128 tiles, 26.6 / 24.1; in two rounds 600 x
-// 1024 -> 25047, 294 tiles, 63.4 / 55.9, 8192 x 768 -> 3072, 384 tiles, 45.6 / 54.5; 8229 x 312 -> 8000, 1056
-// tiles, 73 / 94.  128, one round: the conv over 56 x 56 x 256, 196 tiles, 28.9 / 34.9, over 28 x 28 x 512, 196
-// tiles, 45.8 / 56.6, over 112 x 112 x 128, 196 tiles, 20.3 / 23.5; 2048 x 1024 -> 1024, 128 tiles, 12.3 / 11.7; in two
-// rounds only short K: 8192 x 256 -> 1024 12.3 / 14.2, 8192 x 512 -> 1024 16.2 / 17.3, 8192 x 1024 -> 1024 25.0 /
-// 24.1, the conv over 56 x 56 x 256, 392 tiles, 50 / 44.
+// 1024 -> 25047, 294 tiles, 63.4 / 55.9, 5612 x 512 -> 3526, 308 tiles, 0.85 of there, convs of 311 to 320 tiles
+// 0.86 (1x1, K 512) to 1.06 (3x3, K 576) of there, of 328 tiles 0.88, 8192 x 768 -> 3072, 384 tiles, 45.6 / 54.5;
+// 8229 x 312 -> 8000, 1056 tiles, 73 / 94.
+// Rows past M count too: gemm_kernel holds two 128 x 128 tiles a CU, so a product whose 128 x 128 tiles take
+// no more rounds of 512 than its 256 x 256 tiles take of 256 stays there: 384 x 1024 -> 18000, 423 of 512, 25.5 / 22.7,
+// 96 x 1024 -> 48000, 375, 27.4 / 21.5, 288 x 1024 -> 40000 in two rounds, 939 of 1024, 46.8 / 41.3; and
+// 320 x 1024 -> 22000, 516, 0.82 of there, 256 x 1024 -> 40000, 626, 26.9 / 35.4.
+// 128, one round: the conv over 56 x 56 x 256, 196 tiles, 28.9 / 34.9, over 28 x 28 x 512, 196
+// tiles, 45.8 / 56.6, over 112 x 112 x 128, 196 tiles, 20.3 / 23.5; 2048 x 1024 -> 1024, 128 tiles, 12.3 / 11.7; few
+// rows too, whose time is the weights': 1 x 256 -> 18000 6.2 / 8.2, 1 x 1024 -> 32000 14.0 / 15.6, 17 x 1024 -> 18000
+// 12.4 / 16.2, 64 x 1024 -> 32000 15.4 / 20.6, 128 x 1024 -> 18000 13.0 / 14.7.  gemm_kernel's 128 x 64 tiles in one
+// round are faster still (6314 x 4096 -> 278, 250 of them, 35.5 / 31.9; 6588 x 768 -> 267, 260, 0.79 of there).
+// 128 in more rounds: 17 to 64 rows, whose other tiles split K (64 x 1024 -> 40000 23.3 / 28.2, 17 x 512 -> 48000
+// 15.3 / 18.6); else only short K: 8192 x 256 -> 1024 12.3 / 14.2, 8192 x 512 -> 1024 16.2 / 17.3, 16 x 512 -> 56000
+// 15.7 / 20.1, 129 x 512 -> 32000 0.99 of there (25000 1.04), 65 x 512 -> 56000 16.0 / 15.3, 8192 x 1024 -> 1024 25.0 / 24.1, the conv over 56 x 56 x 256, 392
+// tiles, 50 / 44, 1 x 1024 -> 40000 22.8 / 20.2.
+int pp_tile_size(int64_t M, int N, int K) {
+    if (K < 256) return 0;
+    const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), rounds = (tiles + kCUs - 1) / kCUs;
+    const int64_t small = ((M + 127) / 128) * ((N + 127) / 128), srounds = (small + kCUs - 1) / kCUs;
+    if (N >= 192 && small > 2 * kCUs * rounds &&
+        (rounds == 1 ? tiles >= 140 : tiles * 10 >= rounds * kCUs * 6))
+        return 256;
+    if (N < 96 || ((M + 127) / 128) * ((N + 63) / 64) <= kCUs) return 0;
+    if (srounds == 1) return small >= 140 ? 128 : 0;
+    if (M > 16 && M <= 64) return 128;
+    return K <= 512 && small * 4 >= srounds * kCUs * 3 && (M <= 64 || M > 128) ? 128 : 0;
+}
+
+// The tile of an operator that runs on gemm_pp_kernel (0: it does not)
 static int pp_tile(const GemmParams& p) {
     // (the output span is addressed with 32-bit offsets, below the out-of-range offset 2^31)
     const int64_t c_span = ((p.M - 1) * p.ldc + p.N) * (p.out_f32 ? 4 : 2);
@@ -1767,12 +1792,7 @@ static int pp_tile(const GemmParams& p) {
     if (p.conv && (p.cs % 64 != 0 || p.kh * p.kw > 32 || p.pad >= p.img_w ||
                    int64_t(p.a_bytes) + (int64_t(p.pad) * p.img_w + p.pad) * p.cs * 2 >= (int64_t(1) << 31)))
         return 0;
-    if (p.K < 256) return 0;
-    const int64_t tiles = ((p.M + 255) / 256) * ((p.N + 255) / 256), rounds = (tiles + kCUs - 1) / kCUs;
-    if (p.N >= 192 && (rounds == 1 ? tiles >= 140 : tiles * 10 >= rounds * kCUs * 6)) return 256;
-    const int64_t small = ((p.M + 127) / 128) * ((p.N + 127) / 128), srounds = (small + kCUs - 1) / kCUs;
-    if (p.N >= 96 && (srounds == 1 ? small >= 140 : p.K <= 512 && small * 4 >= srounds * kCUs * 3)) return 128;
-    return 0;
+    return pp_tile_size(p.M, p.N, p.K);
 }
 
 template <int TILE>

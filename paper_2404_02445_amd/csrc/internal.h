@@ -128,6 +128,9 @@ struct GemmParams {
 // only -- never of the sub-slice count -- so sub-sliced launches reduce in
 // the same order as the unsplit one.
 int gemm_splits(int64_t M, int N, int K, int dtype, int epi);
+// Tile edge (256 or 128) of the two-group kernel for a bf16 (M, N, K) product or conv, 0 where gemm_kernel runs
+// it.  Like the split-K factor a function of the shape only.
+int pp_tile_size(int64_t M, int N, int K);
 inline size_t gemm_partial_bytes(int64_t M, int N, int splits) {
     return splits > 1 ? static_cast<size_t>(splits) * static_cast<size_t>(M) * static_cast<size_t>(N) * 4 : 0;
 }

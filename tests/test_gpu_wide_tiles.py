@@ -50,3 +50,21 @@ def test_conv_edges(n, c, hw, cout, k, stride, pad, residual):
     assert rel_err(_np(y1), oracle.forward(mod, x)) <= TOL["bf16"]
     yk, _, _ = run_gpu(mod, x, P.make_plan(1, [0], [3]))
     assert torch.equal(yk, y1)
+
+
+@pytest.mark.parametrize("m,k,n,act,ksub", [
+    (1, 256, 18000, "none", 8),      # few rows on the 128-wide tiles: 141 of them, 127 rows empty
+    (16, 320, 18001, "gelu", 3),     # off the 8-column group
+    (65, 264, 18008, "relu", 4),
+    (33, 264, 34000, "none", 8),     # two rounds: 266 tiles
+    (100, 264, 36000, "none", 8),    # too few rows for a 256-wide tile: gemm_kernel's
+    (300, 320, 18000, "none", 8),
+])
+def test_linear_few_rows(m, k, n, act, ksub):
+    bld, x = seq_input_model("bf16", 1, m, k)
+    mod = bld.finish(bld.linear(x, n, act, "lin", "rand", rd=True), 1)
+    ids = seq_ids(1, m)
+    y1, _, _ = run_gpu(mod, ids, P.make_plan(1, [0], [1]))
+    assert rel_err(_np(y1), oracle.forward(mod, ids)) <= TOL["bf16"]
+    yk, _, _ = run_gpu(mod, ids, P.make_plan(1, [0], [ksub]))
+    assert torch.equal(yk, y1)

@@ -382,3 +382,41 @@ def test_split_k_factor_never_exceeds_what_the_reduce_handles():
                     if (K + bk - 1) // bk < 24:
                         assert s == 1, (M, N, K, s)
                     assert fn(M, N, K, dtype, 1) == 1   # the LSTM epilogue never splits
+
+
+def host_rule(symbol, *argtypes):
+    """A host function of the library that a dispatch rule is made of, by its (mangled) name."""
+    fn = getattr(L.lib(), symbol)
+    fn.restype, fn.argtypes = ctypes.c_int, list(argtypes)
+    return fn
+
+
+def pp_tile_size():
+    return host_rule("_ZN5mopar12pp_tile_sizeElii", ctypes.c_int64, ctypes.c_int, ctypes.c_int)
+
+
+@pytest.mark.parametrize("m,n,k,tile", [
+    (1, 40000, 1024, 0), (128, 48000, 1024, 0),      # one 128-row tile: half of a 256-row one is empty
+    (129, 36000, 1024, 256), (320, 22000, 1024, 256),
+    (384, 18000, 1024, 0), (512, 18000, 1024, 256),  # 423 and 564 tiles of 128 x 128, two a CU
+    (384, 40000, 1024, 0), (512, 40000, 1024, 256),  # 939 and 1256 in two rounds
+    (1, 17792, 1024, 0), (1, 17793, 1024, 128), (64, 32000, 1024, 128),
+    (16, 40000, 1024, 0), (17, 40000, 1024, 128), (64, 40000, 1024, 128), (65, 40000, 1024, 0),
+    (6314, 278, 4096, 0), (6588, 267, 768, 128),     # 250 and 260 tiles of 128 x 64
+    (600, 25047, 1024, 0), (5612, 3526, 512, 256),   # 294 and 308 tiles, two rounds
+    (8192, 32000, 255, 0),
+])
+def test_two_group_tile_choice(m, n, k, tile):
+    assert pp_tile_size()(m, n, k) == tile
+
+
+def test_two_group_tiles_never_take_as_many_rounds_as_the_smaller_ones():
+    fn = pp_tile_size()
+    for m in (1, 16, 64, 65, 128, 129, 256, 257, 384, 385, 513, 600, 1000, 2048, 4500, 8192):
+        for n in (96, 192, 278, 427, 1000, 4096, 12422, 18000, 32000, 40000, 64000, 80000):
+            for k in (256, 512, 1024, 4096):
+                tile, cdiv = fn(m, n, k), lambda a, b: -(-a // b)
+                if tile == 256:   # gemm_kernel holds two 128 x 128 tiles a CU
+                    assert cdiv(m, 128) * cdiv(n, 128) > 512 * cdiv(cdiv(m, 256) * cdiv(n, 256), 256), (m, n, k)
+                elif tile == 128:
+                    assert cdiv(m, 128) * cdiv(n, 64) > 256, (m, n, k)
