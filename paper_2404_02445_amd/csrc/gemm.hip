@@ -1850,6 +1850,12 @@ static hipError_t launch_pp(const GemmParams& params, hipStream_t st) {
     return hipGetLastError();
 }
 
+// Whether a bf16 product of more than 64 rows takes 32 x 32 tiles, four times as many, for its `blocks` 64 x 64
+// ones: while those leave at least a quarter of the CUs idle (us, 64 x 64 / 32 x 32 tiles: 1600 x 1024 -> 256, 100
+// blocks, 7.8 / 6.7; 1024 x 768 -> 768, 192, 6.9 / 6.5; 3136 x 1024 -> 256, 196, 8.1 / 8.5; 900 x 1024 -> 1024, 240,
+// 8.2 / 8.7; 3136 x 512 -> 512, 392, 7.4 / 9.1).
+bool tiles_32x32(int64_t blocks) { return blocks * 4 <= kCUs * 3; }
+
 template <typename T>
 static hipError_t dispatch(const GemmParams& p, hipStream_t st) {
     const int width = (p.N + p.ksub - 1) / p.ksub;   // widest sub-slice
@@ -1887,9 +1893,7 @@ static hipError_t dispatch(const GemmParams& p, hipStream_t st) {
     const bool w128 = width >= 128 && (width + 127) / 128 * 128 * 10 <= width * 11;
     if (w128 && blocks(mt, 128) >= kCUs) return launch_cfg<T, 128, 128, 2, 4, 2>(p, width, st);
     if (width >= 64 && blocks(mt, 64) >= kCUs) return launch_cfg<T, 128, 64, 4, 2, 3>(p, width, st);
-    // under 200 blocks of 64 x 64: 32 x 32 tiles, four times as many (ResNet-50 on 2 images of 150 x 150 356 -> 328 us,
-    // its 1x1 convs of stage 3 at batch 8, 100 blocks, 8.2 -> 6.9 us)
-    if (sizeof(T) == 2 && width >= 64 && !p.thin && blocks((p.M + 63) / 64, 64) < 200)
+    if (sizeof(T) == 2 && width >= 64 && !p.thin && tiles_32x32(blocks((p.M + 63) / 64, 64)))
         return launch_cfg<T, 32, 32, 2, 2, 4>(p, width, st);
     if (width >= 64) return launch_cfg<T, 64, 64, 2, 4, 4>(p, width, st);
     if (width >= 32) {

@@ -391,6 +391,11 @@ def host_rule(symbol, *argtypes):
     return fn
 
 
+@pytest.mark.parametrize("blocks,small", [(1, True), (192, True), (193, False), (196, False), (256, False), (392, False)])
+def test_32x32_tiles_while_a_quarter_of_the_cus_idles(blocks, small):
+    assert bool(host_rule("_ZN5mopar11tiles_32x32El", ctypes.c_int64)(blocks) & 1) == small
+
+
 def pp_tile_size():
     return host_rule("_ZN5mopar12pp_tile_sizeElii", ctypes.c_int64, ctypes.c_int, ctypes.c_int)
 
