@@ -1856,6 +1856,17 @@ static hipError_t launch_pp(const GemmParams& params, hipStream_t st) {
 // 8.2 / 8.7; 3136 x 512 -> 512, 392, 7.4 / 9.1).
 bool tiles_32x32(int64_t blocks) { return blocks * 4 <= kCUs * 3; }
 
+// Whether a product of 17 to 64 rows takes 32 x 16 tiles, eight times as many, for its `blocks` 64 x 64 ones
+// (us, 64 x 64 / 32 x 16 tiles).  bf16: under 128 blocks (33 x 768 -> 6000, 94 blocks, 8.0 / 5.7; 64 x 1024 -> 8000, 125,
+// 8.8 / 9.3, 64 x 512 -> 8000 7.3 / 7.1; 64 x 512 -> 12000, 188, 7.5 / 8.2).  float32, whose 64 x 64 tiles pay most for the
+// block sums: up to 32 rows always (17 x 512 -> 7000 15.3 / 7.0, -> 20000 29.0 / 13.9), above while those leave a quarter
+// of their rounds idle (64 x 512 -> 9216, 144 blocks, 16.2 / 13.3; -> 12000, 188, 16.4 / 15.0; -> 16000, 250, 17.0 /
+// 20.2; -> 20000, 313, 31.2 / 24.6).
+bool tiles_32x16(int64_t M, int64_t blocks, bool bf16) {
+    if (bf16) return blocks < kCUs / 2;
+    return M <= 32 || blocks * 4 <= (blocks + kCUs - 1) / kCUs * kCUs * 3;
+}
+
 template <typename T>
 static hipError_t dispatch(const GemmParams& p, hipStream_t st) {
     const int width = (p.N + p.ksub - 1) / p.ksub;   // widest sub-slice
@@ -1872,9 +1883,7 @@ static hipError_t dispatch(const GemmParams& p, hipStream_t st) {
     // the LSTM step: 32 x 16 tiles (twice the blocks of 64 x 16, less LDS each) measured
     // fastest, alone and beside other streams' kernels
     if (p.epi == EPI_LSTM) return launch_cfg<T, 32, 16, 1, 1, 2, 4, 4>(p, width, st);
-    // few blocks of 64 x 64: eight times as many of 32 x 16 (BERT-base's layer on 60 tokens 47.9 -> 40.2 us, a
-    // 49-pixel bottleneck of ResNet-50's last stage 28 -> 25 us, 33 x 6400 -> 1024 -> 1024 -> 1000 29 -> 22.6 us)
-    if (p.M <= 64 && (p.M + 63) / 64 * ((width + 63) / 64) * p.ksub * p.splits < kCUs / 2)
+    if (p.M <= 64 && tiles_32x16(p.M, (width + 63) / 64 * p.ksub * p.splits, sizeof(T) == 2))
         return launch_cfg<T, 32, 16, 1, 1, 2, 4, 4>(p, width, st);
     if (p.M <= 64) {
         if (width >= 64) return launch_cfg<T, 64, 64, 1, 1, 2, 4, 4>(p, width, st);

@@ -88,6 +88,9 @@ def test_pool_of_a_tensor_read_twice_stays_its_own_pass():
     ("f32", 300, 1100, 200, 3),    # split-K with blocked sums
     ("bf16", 33, 520, 130, 4),     # 32 x 16 tiles, ragged
     ("bf16", 64, 72, 1024, 1),
+    ("f32", 33, 100, 9220, 8),     # 32 x 16 tiles, 145 blocks of 64 x 64 unsplit, 152 in sub-slices
+    ("f32", 64, 36, 12300, 4),     # 193 blocks: 64 x 64 tiles
+    ("f32", 17, 36, 16400, 5),     # up to 32 rows always 32 x 16
 ])
 def test_small_products(dt, m, k, n, ksub):
     bld, x = seq_input_model(dt, 1, m, k)

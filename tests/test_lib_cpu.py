@@ -384,16 +384,26 @@ def test_split_k_factor_never_exceeds_what_the_reduce_handles():
                     assert fn(M, N, K, dtype, 1) == 1   # the LSTM epilogue never splits
 
 
-def host_rule(symbol, *argtypes):
+def host_rule(symbol, *argtypes, restype=ctypes.c_int):
     """A host function of the library that a dispatch rule is made of, by its (mangled) name."""
     fn = getattr(L.lib(), symbol)
-    fn.restype, fn.argtypes = ctypes.c_int, list(argtypes)
+    fn.restype, fn.argtypes = restype, list(argtypes)
     return fn
 
 
 @pytest.mark.parametrize("blocks,small", [(1, True), (192, True), (193, False), (196, False), (256, False), (392, False)])
 def test_32x32_tiles_while_a_quarter_of_the_cus_idles(blocks, small):
-    assert bool(host_rule("_ZN5mopar11tiles_32x32El", ctypes.c_int64)(blocks) & 1) == small
+    assert host_rule("_ZN5mopar11tiles_32x32El", ctypes.c_int64, restype=ctypes.c_bool)(blocks) == small
+
+
+@pytest.mark.parametrize("m,blocks,bf16,small", [
+    (64, 127, True, True), (64, 128, True, False),
+    (64, 144, False, True), (33, 192, False, True), (33, 193, False, False), (33, 256, False, False),
+    (33, 313, False, True), (64, 385, False, False), (32, 250, False, True),
+])
+def test_32x16_tiles_of_few_rows(m, blocks, bf16, small):
+    rule = host_rule("_ZN5mopar11tiles_32x16Ellb", ctypes.c_int64, ctypes.c_int64, ctypes.c_bool, restype=ctypes.c_bool)
+    assert rule(m, blocks, bf16) == small
 
 
 def pp_tile_size():
