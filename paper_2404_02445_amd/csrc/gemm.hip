@@ -1688,6 +1688,15 @@ static hipError_t launch_halo(const GemmParams& params, int width, hipStream_t s
 
 constexpr int kCUs = 256;
 
+// Whether a float32 product runs on 32 x 16 tiles with K split over the waves: at most 16 64 x 64 tiles (a batch-1
+// CNN's later convs and its classifier), whose serial K loop counts as much as a block's MFMA time (64 x 768 -> 768 11.5 us on
+// 64 x 64 tiles with four splits, 6.7 here).  Up to 16 rows and over 2048 of k the 16 x 64 tiles with more splits
+// are faster from 9 tiles on (16 x 4096 -> 1024 8.4 there, 9.2 here; -> 512 8.2 there, 7.8 here).
+static bool f32_small_tiles(int64_t M, int N, int K) {
+    const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
+    return tiles <= 16 && !(M <= 16 && K > 2048 && tiles > 8);
+}
+
 int gemm_splits(int64_t M, int N, int K, int dtype, int epi) {
     if (epi != EPI_STD || M * ((N + 3) / 4) >= (int64_t(1) << 31)) return 1;
     const int bk = dtype == MOPAR_BF16 ? 64 : 32;
@@ -1695,14 +1704,37 @@ int gemm_splits(int64_t M, int N, int K, int dtype, int epi) {
     const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);   // reference tiling, independent of k
     // the reduce pass costs about as much as a dozen k stages: split only long K loops
     if (nk < 24) return 1;
-    // (float32 is MFMA-bound: up to 32 stages, 1024 of k, the loop costs less than the reduce pass saves,
-    // and a doubling that leaves the CU with the most tiles as much work only adds that pass.  308 x 768 ->
-    // 2304, 180 tiles: 24.7 us with two splits, 20.4 us with one)
-    if (dtype != MOPAR_BF16 && nk <= 32) return 1;
-    auto load = [&](int64_t sp) { return (tiles * sp + kCUs - 1) / kCUs * 16 / sp; };
     int s = 1;
-    while (s < 16 && tiles * s < kCUs && nk / (2 * s) >= 4 && (dtype == MOPAR_BF16 || load(2 * s) < load(s))) s *= 2;
-    return s;
+    auto split = [&](int most, auto fits) {
+        while (s < most && nk / (2 * s) >= 4 && fits(2 * s)) s *= 2;
+        return s;
+    };
+    if (dtype == MOPAR_BF16) return split(16, [&](int64_t sp) { return tiles * sp < 2 * kCUs; });
+    // float32 is MFMA-bound: splits pay while they put idle CUs to work (us by number of splits, 1 / 2 / 4 / 8).
+    if (f32_small_tiles(M, N, K)) {
+        // 32 x 16 tiles, three rounds of blocks: 1 x 1024 -> 256 7.6 / 7.1 / 6.1 / 5.7, 100 x 4608 -> 512 (128 blocks) 23.6 /
+        // 15.5 / 13.3 / 14.9, 77 (96 blocks) 23.6 / 15.4 / 13.2 / 11.9; one split under 1024 of k (64 x 768 -> 768 6.7 / 7.2 / 7.5),
+        // and up to there where the reduce pass has no whole groups of four columns (1024 x 1024 -> 10 8.5 / 8.8 / 9.0 / 10.8)
+        const int64_t blocks = ((M + 31) / 32) * ((N + 15) / 16);
+        if (nk < 32 || (N % 4 != 0 && nk == 32)) return 1;
+        return split(16, [&](int64_t sp) { return blocks * sp <= 3 * kCUs; });
+    }
+    // 16 x 64 tiles, one round: 16 x 1024 -> 4096 11.3 / 9.5 / 8.1 / 11.0, 1 x 1024 -> 1088 11.2 / 9.2 / 7.5 / 7.0
+    if (M <= 16) return split(16, [&](int64_t sp) { return tiles * sp <= kCUs; });
+    if (M <= 64) {
+        // tiles of 32 x 16 up to 192 blocks of 64 x 64, which up to 1024 of k need no splits (64 x 768 -> 2304 8.5 / 9.7 /
+        // 13.1, 64 x 1024 -> 1088 7.8 / 9.0 / 8.4); past it half a round of the larger ones (64 x 2048 -> 1088 12.3 / 12.2 / 10.7 /
+        // 13.2, 64 x 3072 -> 2304 23.9 / 20.1 / 23.5, 64 x 3072 -> 6144 33.9 / 39.9), and four splits where they
+        // are one round (33 x 4096 -> 4096 31.2 / 33.6 / 28.7)
+        if (nk <= 32) return 1;
+        if (M > 32 && nk > 64 && tiles > 48 && tiles <= 64) return 4;
+        return split(16, [&](int64_t sp) { return tiles * sp < kCUs / 2; });
+    }
+    // 64 x 64 tiles, one round: 77 x 768 -> 768 (24 tiles) 18.7 / 13.0 / 9.7, 308 x 768 -> 768 (60) 18.9 / 13.9 / 11.6 / 13.4,
+    // 77 x 768 -> 2304 (72) 18.9 / 13.7 / 14.1, 512 x 1024 -> 1024 (128) 24.1 / 19.1 / 20.7, 308 x 768 -> 2304 (180) 19.3 / 22.5.
+    // From 1536 of k on also into a second round: 768 x 2048 -> 768 (144) 44.4 / 42.4 / 44.7, 512 x 3072 -> 768 (96) 64.4 / 37.4 /
+    // 35.2; at 1536 the same (34.3 / 34.3 / 36.6).  More than eight are slower (77 x 3072 -> 768 14.0, with sixteen 14.8)
+    return split(8, [&](int64_t sp) { return tiles * sp <= (nk > 48 ? 2 * kCUs - 1 : kCUs); });
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int NS, int KH = 1, int KS = 1>
@@ -1874,9 +1906,7 @@ static hipError_t dispatch(const GemmParams& p, hipStream_t st) {
         const int tile = pp_tile(p);
         if (tile) return tile == 256 ? launch_pp<256>(p, st) : launch_pp<128>(p, st);
     }
-    // float32 products of at most 16 64 x 64 tiles (a batch-1 CNN's later convs and its classifier): the MFMA time
-    // of a block and its serial K loop both count, so small tiles and K split over the waves
-    if (sizeof(T) == 4 && p.epi == EPI_STD && ((p.M + 63) / 64) * ((p.N + 63) / 64) <= 16)
+    if (sizeof(T) == 4 && p.epi == EPI_STD && f32_small_tiles(p.M, p.N, p.K))
         return launch_cfg<T, 32, 16, 1, 1, 2, 4, 4>(p, width, st);
     // few rows: the four waves split K (four 64-wide sub-stages per stage) instead of the tile
     if (p.M <= 16) return launch_cfg<T, 16, 64, 1, 1, 3, 4, 4>(p, width, st);

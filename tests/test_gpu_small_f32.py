@@ -91,6 +91,10 @@ def test_pool_of_a_tensor_read_twice_stays_its_own_pass():
     ("f32", 33, 100, 9220, 8),     # 32 x 16 tiles, 145 blocks of 64 x 64 unsplit, 152 in sub-slices
     ("f32", 64, 36, 12300, 4),     # 193 blocks: 64 x 64 tiles
     ("f32", 17, 36, 16400, 5),     # up to 32 rows always 32 x 16
+    ("f32", 77, 780, 768, 3),      # 24 tiles: four splits of a ragged K
+    ("f32", 16, 2056, 700, 4),     # 16 x 64 tiles, sixteen splits
+    ("f32", 3, 1028, 72, 2),       # 32 x 16 tiles, eight splits
+    ("f32", 40, 3076, 3200, 3),    # four splits of 64 x 64 tiles
 ])
 def test_small_products(dt, m, k, n, ksub):
     bld, x = seq_input_model(dt, 1, m, k)

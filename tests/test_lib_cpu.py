@@ -435,3 +435,28 @@ def test_two_group_tiles_never_take_as_many_rounds_as_the_smaller_ones():
                     assert cdiv(m, 128) * cdiv(n, 128) > 512 * cdiv(cdiv(m, 256) * cdiv(n, 256), 256), (m, n, k)
                 elif tile == 128:
                     assert cdiv(m, 128) * cdiv(n, 64) > 256, (m, n, k)
+
+
+def test_float32_products_split_k_while_cus_idle():
+    """Over 64 rows and more than 16 tiles of 64 x 64, from 768 of k on: a further split would no longer fit one round of
+    blocks, be shorter than four stages or be the ninth; past 1536 of k a second round may begin."""
+    fn = host_rule("_ZN5mopar11gemm_splitsEliiii", ctypes.c_int64, *[ctypes.c_int] * 4)
+    for m in (65, 77, 100, 154, 256, 308, 512, 768, 1024, 4096):
+        for n in (10, 64, 256, 768, 1000, 2304, 4096):
+            tiles = -(-m // 64) * -(-n // 64)
+            if tiles <= 16:
+                continue
+            for k in (768, 1024, 1536, 1568, 3072, 4608):
+                s, stages = fn(m, n, k, L.MOPAR_F32, 0), -(-k // 32)
+                assert s == 8 or stages // (2 * s) < 4 or 2 * s * tiles > (256 if stages <= 48 else 511), (m, n, k, s)
+                assert s == 1 or s * tiles < 512
+
+
+@pytest.mark.parametrize("m,n,k,splits", [
+    (77, 768, 768, 4), (308, 768, 768, 4), (308, 2304, 768, 1), (512, 1024, 1024, 2),
+    (64, 768, 736, 1), (64, 768, 768, 1), (64, 1024, 1024, 4), (1, 10, 1024, 1), (1, 64, 1024, 8),   # 32 x 16 tiles
+    (16, 1024, 4096, 16), (16, 512, 4096, 16), (16, 4096, 1024, 4),                                   # up to 16 rows
+    (64, 2304, 1024, 1), (64, 2304, 3072, 2), (33, 4096, 4096, 4), (32, 4096, 4096, 1),
+])
+def test_float32_split_factor(m, n, k, splits):
+    assert host_rule("_ZN5mopar11gemm_splitsEliiii", ctypes.c_int64, *[ctypes.c_int] * 4)(m, n, k, L.MOPAR_F32, 0) == splits
