@@ -326,16 +326,16 @@ __device__ __forceinline__ void wait_stages(int r) {
     }
 }
 
-// Waves a SIMD has to hold: the float32 128 x 128 tiles keep two blocks on a CU (their block sums took the conv form
-// to 136 registers, one block: 3x3 convs over 32 x 56 x 56 x 128 293 -> 330 us).
-template <typename T, int BM, int BN>
-constexpr int min_waves() { return sizeof(T) == 4 && BM == 128 && BN == 128 ? 4 : 1; }
+// Waves a SIMD has to hold: the conv form of the float32 128 x 128 tiles keeps two blocks on a CU (its block sums took
+// it to 136 registers, one block: 3x3 convs over 32 x 56 x 56 x 128 292 us with two, 330 with one).
+template <typename T, int BM, int BN, bool CONV>
+constexpr int min_waves() { return sizeof(T) == 4 && BM == 128 && BN == 128 && CONV ? 4 : 1; }
 
 // KS > 1: the KS waves of a block share one wave tile (the whole block tile) and split K
 // instead: a stage holds KH = KS sub-stages and wave w computes sub-stage w of each, so the
 // serial K loop is KS times shorter; the waves' sums are added in wave order at the end.
 template <typename T, int BM, int BN, int WM, int WN, int NS, int KH, int KS, bool CONV>
-__global__ __launch_bounds__(WM * WN * KS * 64, (min_waves<T, BM, BN>())) void gemm_kernel(const GemmParams p) {
+__global__ __launch_bounds__(WM * WN * KS * 64, (min_waves<T, BM, BN, CONV>())) void gemm_kernel(const GemmParams p) {
     constexpr int EPC = Elt<T>::EPC;
     constexpr int BK = 8 * EPC;                 // K elements per sub-stage: two 32-wide (bf16) k steps
     constexpr int TM = BM / WM, TN = BN / WN;   // wave tile
