@@ -631,7 +631,25 @@ __global__ __launch_bounds__(WM * WN * KS * 64, (min_waves<T, BM, BN, CONV>())) 
         static_for<FM>([&](auto a) { af[a] = lds_read16_at<a * 2048>(ab); });
         static_for<FN>([&](auto b) { bf[b] = lds_read16_at<b * 2048>(bb); });
     };
-    auto mfmas = [&](u32x4 (&af)[FM], u32x4 (&bf)[FN]) {
+    // float32 sums in blocks of 128 of k (64 per wave where the waves split K), added up in order: a rounding
+    // error that grows with the number of blocks plus the length of one instead of with K (a float32
+    // BERT-base layer on 4 x 77 tokens: 7.0e-7 of the result without, 3.2e-7 with).  They cost 2 to 3 % of a large
+    // product (8192 x 768 -> 3072 290 -> 297 us) and were 7 % on wave tiles of one MFMA tile (3x3 convs over 32 x 64
+    // x 64 x 16 13.6 -> 14.6 us), which add a block's sum to the total under the next block's first MFMAs, from zero;
+    // on larger wave tiles that costs registers, and with them a CU's second block.
+    constexpr bool BLOCKED = sizeof(T) == 4, MERGED = BLOCKED && FM * FN == 1;
+    f32x4 total[BLOCKED ? FM : 1][BLOCKED ? FN : 1];
+    if constexpr (BLOCKED) {
+#pragma unroll
+        for (int a = 0; a < FM; ++a)
+#pragma unroll
+            for (int b = 0; b < FN; ++b) total[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    auto flush = [&](int a, int b) {
+        if constexpr (BLOCKED) total[a][b] += acc[a][b], acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    auto block_ends = [&](int st) { return BLOCKED && st > 0 && st % (KS == 1 ? 4 : 2) == 0; };   // before stage st
+    auto mfmas = [&](u32x4 (&af)[FM], u32x4 (&bf)[FN], auto next_block) {
 #pragma unroll
         for (int a = 0; a < FM; ++a)
 #pragma unroll
@@ -642,6 +660,7 @@ __global__ __launch_bounds__(WM * WN * KS * 64, (min_waves<T, BM, BN, CONV>())) 
                 } else {
                     const f32x4 av = __builtin_bit_cast(f32x4, af[a]);
                     const f32x4 bv = __builtin_bit_cast(f32x4, bf[b]);
+                    if constexpr (decltype(next_block)::value) flush(a, b);
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[e], av[e], acc[a][b], 0, 0, 0);
@@ -649,30 +668,23 @@ __global__ __launch_bounds__(WM * WN * KS * 64, (min_waves<T, BM, BN, CONV>())) 
             }
     };
 
-    // float32 sums in blocks of 128 of k (64 per wave where the waves split K), added up in order: a rounding
-    // error that grows with the number of blocks plus the length of one instead of with K (a float32
-    // BERT-base layer on 4 x 77 tokens: 7.0e-7 of the result without, 3.2e-7 with, 5.0e-7 with the K
-    // splits that kept the sums short before)
-    constexpr bool BLOCKED = sizeof(T) == 4;
-    f32x4 total[BLOCKED ? FM : 1][BLOCKED ? FN : 1];
-    if constexpr (BLOCKED) {
+    // the first k step of stage st (block-uniform choice)
+    auto mfmas_first = [&](int st, u32x4 (&af)[FM], u32x4 (&bf)[FN]) {
+        if (MERGED && block_ends(st))
+            mfmas(af, bf, std::true_type{});
+        else
+            mfmas(af, bf, std::false_type{});
+    };
+    auto flush_all = [&]() {
 #pragma unroll
         for (int a = 0; a < FM; ++a)
 #pragma unroll
-            for (int b = 0; b < FN; ++b) total[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    auto flush = [&]() {
-        if constexpr (BLOCKED) {
-#pragma unroll
-            for (int a = 0; a < FM; ++a)
-#pragma unroll
-                for (int b = 0; b < FN; ++b) total[a][b] += acc[a][b], acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+            for (int b = 0; b < FN; ++b) flush(a, b);
     };
     for (int st = 0; st < nst; ++st) {
         const int buf = st % NS;
         const int later = min(NS - 2, nst - 1 - st);   // stages issued after this one
-        if (BLOCKED && st > 0 && st % (KS == 1 ? 4 : 2) == 0) flush();
+        if (!MERGED && block_ends(st)) flush_all();
         wait_stages<LMIN * KH>(later);                 // this wave's share of stage st has landed
         __builtin_amdgcn_s_barrier();                  // every wave's share has; stage st-1 fully consumed
         if (st + NS - 1 < nst) issue_stage(st + NS - 1, (st + NS - 1) % NS);
@@ -689,7 +701,7 @@ __global__ __launch_bounds__(WM * WN * KS * 64, (min_waves<T, BM, BN, CONV>())) 
 #pragma unroll
             for (int b = 0; b < FN; ++b) pin(b0[b]);
             read_frags(hb, 1, a1, b1);
-            mfmas(a0, b0);
+            mfmas_first(st, a0, b0);
         } else if constexpr (FM + FN <= 3) {
             // thin wave tiles: both k steps' fragment reads go out together; LDS reads complete
             // in order, so once at most FM + FN are outstanding the first step's have landed
@@ -700,7 +712,7 @@ __global__ __launch_bounds__(WM * WN * KS * 64, (min_waves<T, BM, BN, CONV>())) 
             for (int a = 0; a < FM; ++a) pin(a0[a]);
 #pragma unroll
             for (int b = 0; b < FN; ++b) pin(b0[b]);
-            mfmas(a0, b0);
+            mfmas_first(st, a0, b0);
             __builtin_amdgcn_sched_barrier(0);         // keep these MFMAs ahead of the next wait
         } else {
             // wide wave tiles: holding both steps' fragments would cost the registers that
@@ -712,18 +724,18 @@ __global__ __launch_bounds__(WM * WN * KS * 64, (min_waves<T, BM, BN, CONV>())) 
 #pragma unroll
             for (int b = 0; b < FN; ++b) pin(b0[b]);
             read_frags(sbase, 1, a1, b1);
-            mfmas(a0, b0);
+            mfmas_first(st, a0, b0);
         }
         lds_wait();
 #pragma unroll
         for (int a = 0; a < FM; ++a) pin(a1[a]);
 #pragma unroll
         for (int b = 0; b < FN; ++b) pin(b1[b]);
-        mfmas(a1, b1);
+        mfmas(a1, b1, std::false_type{});
     }
 
     if constexpr (BLOCKED) {
-        flush();
+        flush_all();
 #pragma unroll
         for (int a = 0; a < FM; ++a)
 #pragma unroll
