@@ -131,7 +131,8 @@ int gemm_splits(int64_t M, int N, int K, int dtype, int epi);
 // Tile edge (256 or 128) of the two-group kernel for a bf16 (M, N, K) product or conv, 0 where gemm_kernel runs
 // it.  Like the split-K factor a function of the shape only.
 int pp_tile_size(int64_t M, int N, int K);
-// tile rules of bf16 products over 64 rows and of products of 17 to 64 rows
+// tile rules of small float32 products, of bf16 products over 64 rows and of products of 17 to 64 rows
+bool f32_small_tiles(int64_t M, int N, int K);
 bool tiles_32x32(int64_t blocks);
 bool tiles_32x16(int64_t M, int64_t blocks, bool bf16);
 inline size_t gemm_partial_bytes(int64_t M, int N, int splits) {

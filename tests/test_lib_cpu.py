@@ -460,3 +460,13 @@ def test_float32_products_split_k_while_cus_idle():
 ])
 def test_float32_split_factor(m, n, k, splits):
     assert host_rule("_ZN5mopar11gemm_splitsEliiii", ctypes.c_int64, *[ctypes.c_int] * 4)(m, n, k, L.MOPAR_F32, 0) == splits
+
+
+@pytest.mark.parametrize("m,n,k,small", [
+    (1024, 16, 144, False), (1024, 16, 36, False), (65, 10, 160, False), (1024, 16, 164, True), (1024, 17, 144, True),
+    (64, 16, 36, True), (1025, 64, 576, False), (1024, 64, 576, True), (16, 1024, 2048, True), (16, 1024, 2052, False),
+    (16, 512, 4096, True), (17, 1024, 4096, True),
+])
+def test_float32_small_tiles(m, n, k, small):
+    rule = host_rule("_ZN5mopar15f32_small_tilesElii", ctypes.c_int64, ctypes.c_int, ctypes.c_int, restype=ctypes.c_bool)
+    assert rule(m, n, k) == small
