@@ -414,7 +414,11 @@ void mopar_pipeline_destroy(mopar_pipeline_t pipe);
  * decode of mopar_model_forward, is launched with its own pair of HIP events
  * that the runtime stamps with that kernel's start and end on the device.  A
  * slot's time is the sum of its kernels' durations: launch gaps between
- * kernels are not counted.  Events are created on first use and reused (no
+ * kernels are not counted.  A timed forward launches the kernels that an
+ * untimed one does: where one kernel does two ops (a first-layer convolution
+ * and the max pool after it), its duration is divided between their slots in
+ * the ratio of the two ops' times in the analytic profile
+ * (mopar_model_profile).  Events are created on first use and reused (no
  * device memory); disabling destroys them.  Not thread-safe with respect to
  * concurrent forwards on the same model. */
 int mopar_model_set_timing(mopar_model_t model, int32_t enable);

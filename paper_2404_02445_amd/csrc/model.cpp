@@ -68,6 +68,7 @@ struct mopar_model_s {
     std::vector<std::pair<hipEvent_t, hipEvent_t>> kev;
     size_t kev_next = 0;
     std::vector<size_t> slot_lo, slot_hi;
+    std::vector<char> slot_two;                 // the slot's kernel also did the next op
     void free_events() {
         for (auto& e : kev) {
             (void)hipEventDestroy(e.first);
@@ -767,14 +768,16 @@ static hipError_t run_stem_pool(const mopar_model_s& m, int i, const Ptrs& P, hi
                        static_cast<int>(z.dims[2]), static_cast<int>(z.dims[3]), op.n_out, y.dims[1], op.act, true, s);
 }
 
-// Runs `fn` (which enqueues work on s), bracketed by the events of `slot` when timing is on.
+// Runs `fn` (which enqueues work on s), bracketed by the events of `slot` when timing is on.  `two`: fn does the
+// next op as well.
 template <typename F>
-static hipError_t timed(const mopar_model_s& mc, int slot, hipStream_t s, F&& fn) {
+static hipError_t timed(const mopar_model_s& mc, int slot, hipStream_t s, F&& fn, bool two = false) {
     auto& m = const_cast<mopar_model_s&>(mc);
     (void)s;
     if (!m.timing || slot < 0 || slot >= static_cast<int>(m.slot_lo.size())) return fn();
     LaunchTimer timer{&m.kev, &m.kev_next, hipSuccess};
     m.slot_lo[slot] = m.kev_next;
+    m.slot_two[slot] = two;
     t_timer = &timer;
     const hipError_t e = fn();
     t_timer = nullptr;
@@ -787,6 +790,7 @@ static void reset_timing(const mopar_model_s& mc) {
     m.kev_next = 0;
     std::fill(m.slot_lo.begin(), m.slot_lo.end(), 0);
     std::fill(m.slot_hi.begin(), m.slot_hi.end(), 0);
+    std::fill(m.slot_two.begin(), m.slot_two.end(), 0);
 }
 
 static int run_layers(const mopar_model_s& m, const mopar_plan& p, int l0, int l1, const Ptrs& P, hipStream_t s) {
@@ -795,10 +799,9 @@ static int run_layers(const mopar_model_s& m, const mopar_plan& p, int l0, int l
         for (int i = m.layer_first[l]; i <= m.layer_last[l]; ++i) {
             if (i == skip) continue;
             const int ksub = m.ops[i].rd ? p.k[l] : 1;
-            // (per-op timing runs the ops one by one: the same bits)
-            const bool fuse = !m.timing && m.info[i].pool_next && i + 1 <= m.layer_last[l1];
-            const hipError_t e = fuse ? run_stem_pool(m, i, P, s)
-                                      : timed(m, i, s, [&] { return run_op(m, i, P, ksub, s); });
+            const bool fuse = m.info[i].pool_next && i + 1 <= m.layer_last[l1];
+            const hipError_t e = timed(
+                m, i, s, [&] { return fuse ? run_stem_pool(m, i, P, s) : run_op(m, i, P, ksub, s); }, fuse);
             if (e != hipSuccess) return hip_check(e, "kernel launch");
             if (fuse) skip = i + 1;
         }
@@ -812,6 +815,7 @@ int set_timing_impl(mopar_model_s* m, int32_t enable) {
     m->timing = enable != 0;
     m->slot_lo.assign(enable ? n : 0, 0);
     m->slot_hi.assign(enable ? n : 0, 0);
+    m->slot_two.assign(enable ? n : 0, 0);
     return MOPAR_OK;
 }
 
@@ -824,8 +828,10 @@ int timing_slots_impl(const mopar_model_s* m, int32_t* n) {
 int op_times_impl(const mopar_model_s* m, float* ms, int32_t n) {
     if (!m || !ms) return set_error(MOPAR_E_ARG, "mopar_model_op_times: null argument");
     if (!m->timing) return set_error(MOPAR_E_ARG, "mopar_model_op_times: timing is not enabled");
+    float share = -1.0f;                          // of an op done by the kernel of the one before it
     for (int32_t i = 0; i < n; ++i) {
-        ms[i] = -1.0f;
+        ms[i] = share;
+        share = -1.0f;
         if (i >= static_cast<int32_t>(m->slot_lo.size()) || m->slot_hi[i] <= m->slot_lo[i]) continue;
         float sum = 0.0f;
         for (size_t k = m->slot_lo[i]; k < m->slot_hi[i]; ++k) {
@@ -835,6 +841,13 @@ int op_times_impl(const mopar_model_s* m, float* ms, int32_t n) {
             rc = hip_check(hipEventElapsedTime(&t, m->kev[k].first, m->kev[k].second), "hipEventElapsedTime");
             if (rc) return rc;
             sum += t;
+        }
+        if (m->slot_two[i]) {
+            double mem, here, next;
+            op_profile(*m, m->ops[i], &mem, &here);
+            op_profile(*m, m->ops[i + 1], &mem, &next);
+            share = static_cast<float>(sum * (next / (here + next)));
+            sum -= share;
         }
         ms[i] = sum;
     }

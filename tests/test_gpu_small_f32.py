@@ -43,7 +43,7 @@ def test_first_layer_conv_and_pool(n, c, hw, cout, pad, act):
     plan = P.make_plan(1, [0], [1])
     y, _, _ = run_gpu(m, x, plan)
     assert rel_err(_np(y), oracle.forward(m, x)) <= TOL["bf16"]
-    # conv and pool run one by one while ops are timed: the same bits
+    # while ops are timed: the same bits, and a time for both ops
     sm = P.SlicedModel(m)
     sm.set_timing(True)
     out = sm.forward(plan, torch.from_numpy(np.ascontiguousarray(x)).cuda(), sm.alloc_output(), ws=sm.alloc_workspace(plan))
@@ -107,3 +107,42 @@ def test_small_products(dt, m, k, n, ksub):
     assert rel_err(_np(y1), oracle.forward(mod, ids)) <= TOL[dt]
     yk, _, _ = run_gpu(mod, ids, P.make_plan(1, [0], [ksub]))
     assert torch.equal(yk, y1)
+
+
+def two_node_stem(n=2, hw=(50, 62)):
+    b = synth._Builder("stem3", "bf16", n, 19)
+    x = b.tensor((n, 3, *hw), "f32")
+    b.new_layer("conv")
+    y = b.conv(x, 24, 7, 2, 3, "relu", "c", bn_fold=True)
+    b.new_layer("pool")
+    return b.finish(b.maxpool(y, 3, 2, 1, "p"), 1), synth.random_tensor((n, 3, *hw), "f32", seed=24)
+
+
+def test_first_layer_conv_and_pool_of_two_nodes():
+    """One kernel where both nodes sit in a slice, two where a cut parts them: the same bits."""
+    m, x = two_node_stem()
+    y1, _, _ = run_gpu(m, x, P.make_plan(2, [1], [1, 1]))
+    y2, _, _ = run_gpu(m, x, P.make_plan(2, [0, 1], [1, 1]), "raw")
+    assert rel_err(_np(y1), oracle.forward(m, x)) <= TOL["bf16"]
+    assert torch.equal(y1, y2)
+
+
+def test_timing_runs_the_kernels_of_an_untimed_forward():
+    m, x = two_node_stem()
+    sm, plan = P.SlicedModel(m), P.make_plan(2, [1], [1, 1])
+    xin = torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    ws, outs, left = sm.alloc_workspace(plan), [], []
+    for timing in (False, True):
+        sm.set_timing(timing)
+        ws.fill_(0x5A)
+        outs.append(sm.forward(plan, xin, sm.alloc_output(), ws=ws))
+        torch.cuda.synchronize()
+        left.append(ws.clone())
+    assert torch.equal(outs[0], outs[1])
+    # the conv's own result, which the one kernel keeps to itself, goes to the workspace in neither
+    assert torch.equal(left[0], left[1]) and bool((left[1] == 0x5A).all())
+    conv, pool = sm.op_times()[0]
+    prof = [t for _, t, _, _ in sm.profile()]
+    assert conv > 0 and pool > 0 and abs(pool / conv - prof[1] / prof[0]) < 1e-3 * pool / conv
+    tp = sm.measure(xin, k_max=1, reps=3, ws=ws)
+    assert tp[0][0] > 0 and tp[1][0] > 0
