@@ -793,15 +793,16 @@ static void reset_timing(const mopar_model_s& mc) {
     std::fill(m.slot_two.begin(), m.slot_two.end(), 0);
 }
 
-static int run_layers(const mopar_model_s& m, const mopar_plan& p, int l0, int l1, const Ptrs& P, hipStream_t s) {
+// The ops of nodes l0 .. l1 with k[l] sub-slices; `record` keeps their times where timing is on
+static int run_layers(const mopar_model_s& m, const int32_t* k, int l0, int l1, const Ptrs& P, hipStream_t s, bool record) {
     int skip = -1;                                // an op done in the pass of the one before it
     for (int l = l0; l <= l1; ++l)
         for (int i = m.layer_first[l]; i <= m.layer_last[l]; ++i) {
             if (i == skip) continue;
-            const int ksub = m.ops[i].rd ? p.k[l] : 1;
+            const int ksub = m.ops[i].rd ? k[l] : 1;
             const bool fuse = m.info[i].pool_next && i + 1 <= m.layer_last[l1];
-            const hipError_t e = timed(
-                m, i, s, [&] { return fuse ? run_stem_pool(m, i, P, s) : run_op(m, i, P, ksub, s); }, fuse);
+            auto run = [&] { return fuse ? run_stem_pool(m, i, P, s) : run_op(m, i, P, ksub, s); };
+            const hipError_t e = record ? timed(m, i, s, run, fuse) : run();
             if (e != hipSuccess) return hip_check(e, "kernel launch");
             if (fuse) skip = i + 1;
         }
@@ -865,7 +866,7 @@ int slice_forward_impl(const mopar_model_s* m, const mopar_plan* p, int32_t s, c
     const int l0 = s == 0 ? 0 : p->slice_end[s - 1] + 1, l1 = p->slice_end[s];
     Ptrs P{m, static_cast<unsigned char*>(ws), in, s == 0 ? m->input : m->layer_out[l0 - 1], out, m->layer_out[l1]};
     reset_timing(*m);
-    return run_layers(*m, *p, l0, l1, P, static_cast<hipStream_t>(stream));
+    return run_layers(*m, p->k, l0, l1, P, static_cast<hipStream_t>(stream), true);
 }
 
 // ---------------------------------------------------------------------------
@@ -1053,7 +1054,7 @@ int model_forward_impl(const mopar_model_s* m, const mopar_plan* p, const mopar_
                            "boundary decode");
             if (rc) return rc;
         }
-        rc = run_layers(*m, *p, l0, l1, P, st);
+        rc = run_layers(*m, p->k, l0, l1, P, st, true);
         if (rc) return rc;
         if (s + 1 < S) {   // encode this slice's outputs into the boundary buffers
             rc = hip_check(timed(*m, slot0 + 2 * s, st, [&] { return hand_off(s, true); }), "boundary encode");
@@ -1238,12 +1239,8 @@ static int enqueue_batch(mopar_pipeline_s* pp, int rep, int r, const void* in, v
                 if (rc) return rc;
             }
         }
-        for (int l = l0; l <= l1; ++l)
-            for (int i = m.layer_first[l]; i <= m.layer_last[l]; ++i) {
-                const int ksub = m.ops[i].rd ? pp->k[l] : 1;
-                rc = hip_check(run_op(m, i, P, ksub, st), "kernel launch");
-                if (rc) return rc;
-            }
+        rc = run_layers(m, pp->k.data(), l0, l1, P, st, false);
+        if (rc) return rc;
         if (s < S - 1) {
             const int c = s, slot = r * ncut + c;
             // the slot is free once the previous batch using it has been decoded
