@@ -60,7 +60,7 @@ struct mopar_model_s {
     std::vector<int> layer_out;                 // tensor leaving each node
     std::vector<std::vector<int>> cross;        // per cut j (after node j): node outputs of nodes <= j
                                                 // that nodes > j read, ascending tensor id
-    std::vector<size_t> offset;                 // workspace offset per tensor (SIZE_MAX: not in ws)
+    std::vector<size_t> offset;                 // workspace offset per tensor (SIZE_MAX: not in ws, or never stored)
     size_t ws_bytes;
     // measurement (timing slots: ops, then encode / decode per cut): each kernel launched
     // inside a slot gets an event pair from kev; a slot owns the pairs [slot_lo, slot_hi)
@@ -341,6 +341,7 @@ static int validate_and_build(mopar_model_s& m) {
                     return set_error(MOPAR_E_UNSUPPORTED, nm + ": a GEMM operand reaches 2 GiB");
                 if (!wcheck(op.w, op.n_out * inf.K, "w") || !wcheck(op.b, op.n_out, "b"))
                     return set_error(MOPAR_E_ARG, nm + ": weight offsets out of range or not 16-byte aligned");
+                if (inf.stem) break;               // (no scratch: it reads the image as it is and splits nothing)
                 if (xin) inf.temps.push_back(static_cast<size_t>(x.dims[0] * x.dims[2] * x.dims[3] * inf.cs) * es);
                 inf.splits = conv_halo_ok(m.dtype, op.kh, op.kw, op.stride, op.pad, inf.cs, op.n_out,
                                           static_cast<int>(ho), static_cast<int>(wo), inf.M)
@@ -516,6 +517,8 @@ static int validate_and_build(mopar_model_s& m) {
         inf.temp_off.clear();
         for (size_t tb : inf.temps) inf.temp_off.push_back(alloc(tb, i));
         const int t = m.ops[i].out;
+        // a conv whose pool runs in the same pass and node, where no cut can part them, stores no result
+        if (inf.pool_next && m.ops[i + 1].layer == m.ops[i].layer) continue;
         if (t != m.output && m.offset[t] == SIZE_MAX) {   // first writer allocates (concatenations)
             const size_t bytes = static_cast<size_t>(numel(m.tensors[t])) * es;
             m.offset[t] = alloc(bytes, std::max(last_use[t], i));
@@ -614,6 +617,7 @@ static hipError_t run_op(const mopar_model_s& m, int i, const Ptrs& P, int ksub,
     const auto& x = m.tensors[op.in0];
     const auto& y = m.tensors[op.out];
     const int dt = m.dtype;
+    if (op.out != P.out_tid && m.offset[op.out] == SIZE_MAX) return hipErrorInvalidValue;   // a result without a place
     switch (op.kind) {
         case MOPAR_OP_CONV: {
             const void* src = P.get(op.in0);

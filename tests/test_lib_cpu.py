@@ -470,3 +470,21 @@ def test_float32_split_factor(m, n, k, splits):
 def test_float32_small_tiles(m, n, k, small):
     rule = host_rule("_ZN5mopar15f32_small_tilesElii", ctypes.c_int64, ctypes.c_int, ctypes.c_int, restype=ctypes.c_bool)
     assert rule(m, n, k) == small
+
+
+def stem_workspace(act, nodes, n=2, hw=(64, 96), cout=32):
+    b = synth._Builder("stem", "bf16", n, 5)
+    x = b.tensor((n, 3, *hw), "f32")
+    b.new_layer("L0")
+    y = b.conv(x, cout, 7, 2, 3, act, "c", bn_fold=True)
+    if nodes == 2:
+        b.new_layer("L1")
+    m = b.finish(b.maxpool(y, 3, 2, 1, "p"), 1)
+    return P.SlicedModel(m, device="cpu").workspace_bytes(P.make_plan(nodes, [nodes - 1], [1] * nodes))
+
+
+def test_first_layer_conv_and_pool_reserve_only_what_they_store():
+    conv = 2 * 32 * 48 * 32 * 2                  # the conv's result, stored where a cut may part it from its pool
+    assert stem_workspace("relu", 1) == 0
+    assert stem_workspace("relu", 2) == conv
+    assert stem_workspace("gelu", 1) >= conv + 2 * 64 * 96 * 8 * 2   # the general path copies the image channels-last
