@@ -1,4 +1,6 @@
 """Shared helpers of the test suite: small model builders and the error metric."""
+import ctypes
+
 import numpy as np
 
 import synth
@@ -50,3 +52,22 @@ def boundary_codecs(model, cuts, kind="ae"):
     if kind != "ae" or not tids:
         return tids, None
     return tids, synth.make_codec_weights(model, cuts, ratio=ratios, tensors=tids)
+
+
+def host_rule(symbol, *argtypes, restype=ctypes.c_int):
+    """A host function of the library that a dispatch rule is made of, by its (mangled) name."""
+    from paper_2404_02445_amd import _lib
+    fn = getattr(_lib.lib(), symbol)
+    fn.restype, fn.argtypes = restype, list(argtypes)
+    return fn
+
+
+def pp_tile_size(m, n, k):
+    """Tile edge of the two-group bf16 kernel for an (m, n, k) product; 0 where it does not run."""
+    return host_rule("_ZN5mopar12pp_tile_sizeElii", ctypes.c_int64, ctypes.c_int, ctypes.c_int)(m, n, k)
+
+
+def conv_halo_ok(kh, kw, stride, pad, c, n_out, ho, wo, m):
+    """Whether a bf16 conv runs on the patch-staged 3x3 kernel."""
+    fn = host_rule("_ZN5mopar12conv_halo_okEiiiiiiiiil", *[ctypes.c_int] * 9, ctypes.c_int64, restype=ctypes.c_bool)
+    return fn(1, kh, kw, stride, pad, c, n_out, ho, wo, m)   # 1: MOPAR_BF16

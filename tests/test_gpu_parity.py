@@ -154,20 +154,19 @@ def seq_ids(b, s):
     ("f32", 2, 7, 36, 44, "relu", True, 2),
     # few rows: K split across the waves of a block, with split-K and a K tail (2000 = 31*64 + 16)
     ("bf16", 16, 1, 2000, 96, "relu", False, 3),
-    # split-K summed in the GEMM launch (k = 1) against the separate reduce launch (k = 100 sub-slices
-    # need more arrival counters than the op's slot holds): bitwise equal
+    # split-K of one block column a sub-slice: 100 sub-slices of two columns against the unsplit launch
     ("bf16", 16, 1, 2000, 200, "relu", False, 100),
     # M = 40: the 64x64 and 64x16 K-split tiles (k = 1 vs k = 4) must agree bit for bit
     ("bf16", 5, 8, 1504, 70, "gelu", True, 4),
     ("f32", 4, 4, 700, 33, "none", True, 2),
-    # products with at least 1024 tiles of 256 x 256 run on the 32 x 32 MFMA kernel, every
+    # products on the two-group kernel (256 x 256 tiles, which run across sub-slice edges), every
     # sub-slice launch included: 8192 x 256 x 8192 against 1024-column sub-slices
     ("bf16", 16, 512, 256, 8192, "none", False, 8),
     # ragged M (33 tile rows), N and K (312 = 4 x 64 + 56) with residual and GELU, against
     # 500-column sub-slices
     ("bf16", 3, 2743, 312, 8000, "gelu", True, 16),
-    # the persistent launch with groups of four columns cut by the sub-slice edge (2 x 4001
-    # columns: element stores)
+    # a width off the 8-column group (unaligned stores, a last group of two columns), the sub-slice
+    # edge at column 4001
     ("bf16", 4, 2048, 256, 8002, "none", False, 2),
     # BERT-base's FFN1 (4096 x 768 -> 3072, GELU) in its four 768-column sub-slices
     ("bf16", 32, 128, 768, 3072, "gelu", False, 4),
@@ -242,8 +241,8 @@ def test_layernorm_with_residual():
 @pytest.mark.parametrize("dt,seq,heads", [("bf16", 128, 12), ("bf16", 37, 2), ("bf16", 1, 1), ("bf16", 64, 3),
                                            ("bf16", 65, 2), ("bf16", 100, 4), ("f32", 40, 2)])
 def test_attention(dt, seq, heads):
-    # bf16 runs on the matrix cores (64-query tiles, keys padded to 32 and masked), f32 on
-    # the vector units; sequence lengths cover one key, whole and partial query tiles
+    # 64-query tiles on the matrix cores; bf16 masks 128 keys, float32 whole groups of 16;
+    # sequence lengths cover one key, whole and partial query tiles
     bld, x = seq_input_model(dt, 2, seq, 3 * 64 * heads, scale=1.5)
     y = bld.attention(x, heads, "att")
     m = bld.finish(y, 1)

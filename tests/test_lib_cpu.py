@@ -11,7 +11,7 @@ import pytest
 import oracle
 import synth
 from oracle import plan as OP
-from helpers import SMALL
+from helpers import SMALL, host_rule, pp_tile_size
 
 SMALL6 = SMALL[6]
 
@@ -384,13 +384,6 @@ def test_split_k_factor_never_exceeds_what_the_reduce_handles():
                     assert fn(M, N, K, dtype, 1) == 1   # the LSTM epilogue never splits
 
 
-def host_rule(symbol, *argtypes, restype=ctypes.c_int):
-    """A host function of the library that a dispatch rule is made of, by its (mangled) name."""
-    fn = getattr(L.lib(), symbol)
-    fn.restype, fn.argtypes = restype, list(argtypes)
-    return fn
-
-
 @pytest.mark.parametrize("blocks,small", [(1, True), (192, True), (193, False), (196, False), (256, False), (392, False)])
 def test_32x32_tiles_while_a_quarter_of_the_cus_idles(blocks, small):
     assert host_rule("_ZN5mopar11tiles_32x32El", ctypes.c_int64, restype=ctypes.c_bool)(blocks) == small
@@ -406,10 +399,6 @@ def test_32x16_tiles_of_few_rows(m, blocks, bf16, small):
     assert rule(m, blocks, bf16) == small
 
 
-def pp_tile_size():
-    return host_rule("_ZN5mopar12pp_tile_sizeElii", ctypes.c_int64, ctypes.c_int, ctypes.c_int)
-
-
 @pytest.mark.parametrize("m,n,k,tile", [
     (1, 40000, 1024, 0), (128, 48000, 1024, 0),      # one 128-row tile: half of a 256-row one is empty
     (129, 36000, 1024, 256), (320, 22000, 1024, 256),
@@ -422,15 +411,14 @@ def pp_tile_size():
     (8192, 32000, 255, 0),
 ])
 def test_two_group_tile_choice(m, n, k, tile):
-    assert pp_tile_size()(m, n, k) == tile
+    assert pp_tile_size(m, n, k) == tile
 
 
 def test_two_group_tiles_never_take_as_many_rounds_as_the_smaller_ones():
-    fn = pp_tile_size()
     for m in (1, 16, 64, 65, 128, 129, 256, 257, 384, 385, 513, 600, 1000, 2048, 4500, 8192):
         for n in (96, 192, 278, 427, 1000, 4096, 12422, 18000, 32000, 40000, 64000, 80000):
             for k in (256, 512, 1024, 4096):
-                tile, cdiv = fn(m, n, k), lambda a, b: -(-a // b)
+                tile, cdiv = pp_tile_size(m, n, k), lambda a, b: -(-a // b)
                 if tile == 256:   # gemm_kernel holds two 128 x 128 tiles a CU
                     assert cdiv(m, 128) * cdiv(n, 128) > 512 * cdiv(cdiv(m, 256) * cdiv(n, 256), 256), (m, n, k)
                 elif tile == 128:
