@@ -1709,12 +1709,12 @@ constexpr int kCUs = 256;
 // CNN's later convs and its classifier), whose serial K loop counts as much as a block's MFMA time (64 x 768 -> 768 11.5 us on
 // 64 x 64 tiles with four splits, 6.7 here).  Up to 16 rows and over 2048 of k the 16 x 64 tiles with more splits
 // are faster from 9 tiles on (16 x 4096 -> 1024 8.4 there, 9.2 here; -> 512 8.2 there, 7.8 here).  Over 64 rows, up to 16
-// columns and 160 of k, five stages, there is too little K to share out: 64 x 16 tiles (3x3 convs over 32 x 32 x 4 -> 16
-// 3.8 there, 4.2 here, over 32 x 32 x 16 4.9, 5.0; 1024 x 100 -> 10 4.3, 4.6; 1024 x 200 -> 10 and 512 x 144 -> 32 are
-// faster here).
+// columns and 128 of k, four stages, there is too little K to share out: 64 x 16 tiles (3x3 convs over 32 x 32 x 4 -> 16
+// 3.8 there, 4.2 here; 1024 x 100 -> 10 4.3, 4.6; past it the sums shared out are the more exact ones, 1.2e-7 against
+// 2.0e-7 of the result at 144 of k, and as fast: 1024 x 144 -> 16 4.4, 4.5).
 bool f32_small_tiles(int64_t M, int N, int K) {
     const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
-    return tiles <= 16 && !(M <= 16 && K > 2048 && tiles > 8) && !(M > 64 && N <= 16 && K <= 160);
+    return tiles <= 16 && !(M <= 16 && K > 2048 && tiles > 8) && !(M > 64 && N <= 16 && K <= 128);
 }
 
 int gemm_splits(int64_t M, int N, int K, int dtype, int epi) {

@@ -94,8 +94,9 @@ def test_pool_of_a_tensor_read_twice_stays_its_own_pass():
     ("f32", 77, 780, 768, 3),      # 24 tiles: four splits of a ragged K
     ("f32", 16, 2056, 700, 4),     # 16 x 64 tiles, sixteen splits
     ("f32", 3, 1028, 72, 2),       # 32 x 16 tiles, eight splits
-    ("f32", 1000, 144, 16, 3),     # 64 x 16 tiles: two block sums, the second of 16
-    ("f32", 65, 160, 10, 2),
+    ("f32", 1000, 128, 16, 3),     # 64 x 16 tiles, one block sum
+    ("f32", 65, 36, 10, 2),
+    ("f32", 1040, 144, 16, 3),     # 17 tiles: 64 x 16, the second block sum of 16
     ("f32", 40, 3076, 3200, 3),    # four splits of 64 x 64 tiles
 ])
 def test_small_products(dt, m, k, n, ksub):

@@ -451,7 +451,7 @@ def test_float32_split_factor(m, n, k, splits):
 
 
 @pytest.mark.parametrize("m,n,k,small", [
-    (1024, 16, 144, False), (1024, 16, 36, False), (65, 10, 160, False), (1024, 16, 164, True), (1024, 17, 144, True),
+    (1024, 16, 128, False), (1024, 16, 36, False), (65, 10, 100, False), (1024, 16, 132, True), (1024, 17, 36, True),
     (64, 16, 36, True), (1025, 64, 576, False), (1024, 64, 576, True), (16, 1024, 2048, True), (16, 1024, 2052, False),
     (16, 512, 4096, True), (17, 1024, 4096, True),
 ])
