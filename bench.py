@@ -82,7 +82,7 @@ def op_bytes(m, op, es):
     return b
 
 
-GEMM_KINDS = ("conv", "linear", "lstm")        # run on gemm_kernel / conv3_halo_kernel
+GEMM_KINDS = ("conv", "linear", "lstm")        # run on the GEMM, patch-staged conv, stem and LSTM kernels
 
 
 def rd_names(m, rd):
@@ -545,7 +545,8 @@ def run_config(cfg, args, headline):
     if scope:
         roof["traffic_scope"] = scope
     roof.update({
-        "kernel": "the RD ops' launches (gemm_kernel; conv3_halo_kernel for patch-staged 3x3 convs), one "
+        "kernel": "the RD ops' launches (gemm_pp_kernel for large bf16 products, conv3_halo_kernel for "
+                  "patch-staged 3x3 convs, gemm_kernel otherwise), one "
                   "launch per RD op holding its k sub-slices: " + rd_names(m, rd),
         "launches_per_step": len(rd), "flop_per_launch": rd_fl // len(rd),
         "algorithmic_bytes_per_launch": rd_by // len(rd), "avg_launch_us": round(rd_launch_us, 2),

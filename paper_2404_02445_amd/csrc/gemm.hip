@@ -1,6 +1,8 @@
-// MFMA GEMM for gfx950: the resource-dominant operators (conv as implicit GEMM
+// MFMA GEMMs for gfx950: the resource-dominant operators (conv as implicit GEMM
 // over NHWC activations, linear layers), the boundary autoencoder and the
-// LSTM recurrence all run through this kernel.
+// LSTM's products.  gemm_kernel, which this comment describes, takes any of them;
+// gemm_pp_kernel takes large bf16 products and convs, conv3_halo_kernel small 3x3
+// convs (each described at its place).
 //
 //   C[m, n] = epilogue( sum_k A[m, k] * B[n, k] )
 //
@@ -10,12 +12,15 @@
 // Horizontal sub-slicing (the k equal-size sub-slices of an RD operator): a
 // block's sub-slice index selects output columns [lo, hi) and weight rows
 // [lo, hi), split as mopar_subslice_range does; each sub-slice is tiled on its
-// own and masked at hi.  What fixes the arithmetic -- the MFMA shape, the order
-// of the 32-wide k steps, the split-K boundaries (in 64-element units) and the
-// order partial sums are added -- depends only on (M, N, K) and the dtype, never
-// on the tile shape, the stage depth or the sub-slice, so every output element
-// goes through the same fp32 operations whatever k is: sub-sliced output equals
-// the unsplit output bit for bit.
+// own and masked at hi (gemm_pp_kernel's tiles run across the edges instead).
+// What fixes the arithmetic -- the kernel and so the MFMA shape, the order of the
+// k steps, the split-K boundaries (in 64-element units), whether the waves of a
+// block share out K, the blocks that float32 sums are made of and the order
+// partial sums are added -- is a function of the op alone ((M, N, K), dtype, conv
+// geometry), never of the sub-slice count; the rest of a tile's shape and the stage
+// depth may follow the sub-slice.  So every output element goes through the same
+// fp32 operations whatever k is: sub-sliced output equals the unsplit output bit
+// for bit.
 //
 // Data path.  Operands stream from HBM straight into LDS with buffer_load_dwordx4
 // ... lds (16 bytes per lane, no VGPR staging), NS stages deep; a stage holds one
@@ -906,12 +911,13 @@ __global__ __launch_bounds__(WM * WN * KS * 64, (min_waves<T, BM, BN, CONV>())) 
 // tiles ahead (a k tile takes 0.4-0.5 us; gemm_kernel's 128 x 64 tiles 0.6-1 us).
 //
 // A block runs up to kPPChunk tiles; the load stream goes on into the next tile during the last k
-// tiles of the current one, so set-up and first-stage latency are paid once per block.  The 32
+// tiles of the current one, so set-up and first-stage latency are paid once per block (but for the conv forms of 256
+// x 256 tiles, which keep 1 to 17 registers in scratch: they reload them at a change of tile behind a wait for
+// every load in flight).  The 32
 // blocks an XCD runs at a time work on 32 consecutive tiles of its run, in groups of 8 m tiles
 // that share operand rows in its L2.  The results turn through 4 KB of LDS per wave so that a store
 // covers whole rows of the wave's part (128 bytes of bf16 or float32 a row; straight from the accumulators
-// a row got 32 bytes a store: 8192 x 1024 -> 32000 492 -> 473 us, 8000 x 1024 -> 31001 571 -> 530, and the LSTM
-// layer whose recurrence reads the float32 results next 515 -> 475).
+// a row got 32 bytes a store: 8192 x 1024 -> 32000 492 -> 473 us, 8000 x 1024 -> 31001 571 -> 530).
 //
 // Arithmetic: acc = sum over k in 16-wide steps in ascending order from zero, then + (bias +
 // bias2), + residual, activation: a function of the op alone, so tiles run across the edges of
@@ -1495,12 +1501,14 @@ constexpr int HTW = 8;                       // output tile width; its height TH
 
 bool conv_halo_ok(int dtype, int kh, int kw, int stride, int pad, int cs, int n_out, int out_h, int out_w, int64_t m) {
     // Small convs only: at most 2^31 multiply-adds (M x N x K; each of ResNet-50's stride-1 3x3
-    // convs at batch 8 is 0.92 G).  On those the implicit GEMM's large tiles leave CUs idle or
-    // need split-K and a second launch, and this kernel is faster (stages 3 and 4: 9.0-10.0
-    // against 13.5-16.6 us and 12.1-12.2 against 14.6-15.2 us).  On larger convs the patch,
-    // re-read for every 16 output channels, and the small tiles lose to the GEMM, measured:
-    // VGG-16 at batch 16, 7.4-29.6 G multiply-adds, 51-192 us here against 36-74 us; and over
-    // images above 56 x 56.
+    // convs at batch 8 is 0.92 G).  On those the implicit GEMM's large tiles leave CUs idle or need split-K and
+    // a second launch.  On larger ones the patch, re-read for every 16 output channels, and the small tiles lose to it;
+    // and over images above 56 x 56.  Measured in four sub-slices (us, here / the implicit GEMM's best tiles), both
+    // sides of the line: 128 channels over 28 x 28, batch 8 7.6 / 10.4, 16 (1.8 G) 12.0 / 12.8, 24 (2.8 G) 16.5 / 13.9; 256 over
+    // 14 x 14, batch 8 8.3 / 13.2, 16 15.3 / 17.2, 24 22.1 / 19.0, 32 28.2 / 19.2; 512 over 7 x 7, batch 8 12.4 / 14.2, 16 13.6 / 17.0, 24
+    // 23.3 / 23.2, 32 26.0 / 24.4, 64 50.7 / 33.5.  64 channels over 56 x 56 are ahead past it too (batch 8 8.2 / 10.2, 32 22.2 / 33.4), and the
+    // GEMM is ahead before it where 8 x 8 tiles fit badly (10 x 10 of 256 channels, batch 16 14.9 / 13.3) or blocks are
+    // few (512 over 14 x 14, batch 1 11.3 / 10.8).
     if (!(dtype == MOPAR_BF16 && kh == 3 && kw == 3 && stride == 1 && pad == 1 && cs % 64 == 0 && cs <= 512 &&
           n_out >= 1 && n_out <= 512 && out_h >= 7 && out_w >= 7 && int64_t(out_h) * out_w <= 56 * 56 && m >= 0 &&
           m < (int64_t(1) << 31)))
@@ -1699,8 +1707,10 @@ static hipError_t launch_halo(const GemmParams& params, int width, hipStream_t s
 }
 
 // ---------------------------------------------------------------------------
-// Tile selection.  All shapes share the K loop, so the choice only affects
-// speed, never the bits of a result.
+// Tile selection.  Tiles of gemm_kernel with the same number of waves along K share the K
+// loop and give the same bits, so a choice among them may follow the sub-slice width.
+// What changes bits (pp_tile, conv_halo_ok, gemm_splits, and K shared out over the waves: up to 64 rows,
+// and f32_small_tiles) depends on the op alone.
 // ---------------------------------------------------------------------------
 
 constexpr int kCUs = 256;

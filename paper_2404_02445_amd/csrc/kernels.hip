@@ -865,8 +865,8 @@ hipError_t launch_codec_narrow(const void* x, const void* w, const void* b, void
 //
 // ResNet-50's stem at batch 32 (224 x 224): 75 us as three kernels, 34.8 us here; at batch 8 33.6 -> 11.5 us.
 // It is bound by the latency of a block's phases (patch, weights, MFMAs, pool) with three blocks per
-// CU: 1568 blocks in two rounds.  Loads under branches cost most of it before they went through buffer
-// resources (52 us), weights read in fragment order 3 us more.
+// CU: 1568 blocks, two rounds of 768 and 32 more.  Loads under branches cost most of it before they
+// went through buffer resources (52 us), weights read in fragment order 3 us more.
 // ---------------------------------------------------------------------------
 namespace {
 
