@@ -1825,9 +1825,11 @@ static hipError_t launch_cfg(const GemmParams& params, int width, hipStream_t st
 // 12.4 / 16.2, 64 x 1024 -> 32000 15.4 / 20.6, 128 x 1024 -> 18000 13.0 / 14.7.  gemm_kernel's 128 x 64 tiles in one
 // round are faster still (6314 x 4096 -> 278, 250 of them, 35.5 / 31.9; 6588 x 768 -> 267, 260, 0.79 of there).
 // 128 in more rounds: 17 to 64 rows, whose other tiles split K (64 x 1024 -> 40000 23.3 / 28.2, 17 x 512 -> 48000
-// 15.3 / 18.6); else only short K: 8192 x 256 -> 1024 12.3 / 14.2, 8192 x 512 -> 1024 16.2 / 17.3, 16 x 512 -> 56000
-// 15.7 / 20.1, 129 x 512 -> 32000 0.99 of there (25000 1.04), 65 x 512 -> 56000 16.0 / 15.3, 8192 x 1024 -> 1024 25.0 / 24.1, the conv over 56 x 56 x 256, 392
-// tiles, 50 / 44, 1 x 1024 -> 40000 22.8 / 20.2.
+// 15.3 / 18.6); else only short K, 75 % of the rounds: 8192 x 256 -> 1024 12.3 / 14.2, 257 x 256 -> 18000, 423 tiles, 10.8 /
+// 11.8, 16 x 512 -> 56000 15.7 / 20.1, 7209 x 512 -> 798, 399, 0.85 of there (65 x 512 -> 56000 16.0 / 15.3, 8192 x 1024 -> 1024
+// 25.0 / 24.1, the conv over 56 x 56 x 256, 392 tiles, 50 / 44, 1 x 1024 -> 40000 22.8 / 20.2); past 256 of k 90 % where
+// gemm_kernel's tiles are 128 wide: 8192 x 512 -> 1024, 512 tiles, 16.2 / 17.3, 256 x 512 -> 32000, 500, 0.99 of there, 129 x
+// 512 -> 28000, 438, 1.02, -> 25000, 392, 1.04.
 int pp_tile_size(int64_t M, int N, int K) {
     if (K < 256) return 0;
     const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), rounds = (tiles + kCUs - 1) / kCUs;
@@ -1838,7 +1840,9 @@ int pp_tile_size(int64_t M, int N, int K) {
     if (N < 96 || ((M + 127) / 128) * ((N + 63) / 64) <= kCUs) return 0;
     if (srounds == 1) return small >= 140 ? 128 : 0;
     if (M > 16 && M <= 64) return 128;
-    return K <= 512 && small * 4 >= srounds * kCUs * 3 && (M <= 64 || M > 128) ? 128 : 0;
+    const bool wide = M > 64 && (N + 127) / 128 * 128 * int64_t(10) <= N * int64_t(11);
+    const int share = K > 256 && wide ? 90 : 75;
+    return K <= 512 && small * 100 >= srounds * kCUs * share && (M <= 64 || M > 128) ? 128 : 0;
 }
 
 // The tile of an operator that runs on gemm_pp_kernel (0: it does not)

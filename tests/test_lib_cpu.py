@@ -408,6 +408,9 @@ def test_32x16_tiles_of_few_rows(m, blocks, bf16, small):
     (16, 40000, 1024, 0), (17, 40000, 1024, 128), (64, 40000, 1024, 128), (65, 40000, 1024, 0),
     (6314, 278, 4096, 0), (6588, 267, 768, 128),     # 250 and 260 tiles of 128 x 64
     (600, 25047, 1024, 0), (5612, 3526, 512, 256),   # 294 and 308 tiles, two rounds
+    (160, 25000, 512, 0), (256, 32000, 512, 128),    # 392 and 500 tiles of 128 in two rounds
+    (16, 56000, 512, 128), (1, 40000, 512, 0),       # 438 and 313
+    (160, 25000, 256, 128), (7209, 798, 512, 128),   # 392, a shorter K; 399, widths gemm_kernel takes in 64s
     (8192, 32000, 255, 0),
 ])
 def test_two_group_tile_choice(m, n, k, tile):
